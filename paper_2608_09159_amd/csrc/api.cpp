@@ -90,7 +90,8 @@ struct Instance {
   DevProblem P{};
   DevVec V{};
   Ctl* ctl = nullptr;
-  Barrier* bar = nullptr;
+  unsigned long long* comm = nullptr;   // the grid's exchange words (Comm), cleared before epoch 1
+  unsigned epoch = 0;          // all-reduces done on them
   TraceBufs T{};
   double* scratch = nullptr;   // power iteration scratch
   double qmax = 0.0;
@@ -98,7 +99,7 @@ struct Instance {
   int lds_bytes = 0;           // dynamic LDS per workgroup for its slice of R
   int* at_cls_perm = nullptr;  // all A^T rows by length class (skewed rows; setup products)
   long at_cls_seg[6] = {0, 0, 0, 0, 0, 0};
-  size_t bar_bytes = 0;
+  size_t comm_bytes = 0;
   long n_warm = 0;
   int* d_perm = nullptr;       // caller index of each internal coordinate (null: same order)
   double* io = nullptr;        // IO_DOUBLES of scratch for the dual-slack output
@@ -320,7 +321,6 @@ int upload_instance(Handle* h, Instance* I) {
   }
   I->scratch = B.alloc<double>(2048 + 2);
   I->ctl = B.alloc<Ctl>(1);
-  I->bar = nullptr;   // allocated with the grid size below
   if (h->s.trace_iters > 0) {
     long cap = h->s.trace_iters;
     I->T.cap = (int)cap;
@@ -726,9 +726,8 @@ int upload_instance(Handle* h, Instance* I) {
       }
     }
   }
-  V.partials = B.alloc<double>((size_t)SL_COUNT * G);
-  I->bar_bytes = sizeof(Barrier) + sizeof(unsigned) * (size_t)G * BAR_STRIDE;
-  I->bar = (Barrier*)B.alloc<char>(I->bar_bytes);
+  I->comm_bytes = sizeof(unsigned long long) * (COMM_HEAD + 2 * SL_COUNT * ((size_t)G + COMM_COPIES));
+  I->comm = (unsigned long long*)B.alloc<char>(I->comm_bytes);
   I->d_perm = H.perm.empty() ? nullptr : B.upload(H.perm);
   I->io = B.alloc<double>(IO_DOUBLES);
   if (B.err != hipSuccess) return PDHCG_E_MEM;
@@ -1000,7 +999,6 @@ void carve_instance(const HostInstance& H, int trace_cap, bool avg, Carve& c, In
     V.yb = c.take<double>(m);
     V.Axb = c.take<double>(m);
   }
-  V.partials = c.take<double>(SL_COUNT);
   D.T = TraceBufs{};
   if (trace_cap > 0) {
     D.T.cap = trace_cap;
@@ -1448,14 +1446,15 @@ int pdhcg_solve(pdhcg_handle* h, const double* x0, const double* y0, pdhcg_resul
   std::memset(&c0, 0, sizeof(c0));
   HIPCHK(reset_cone_failure(st));
   HIPCHK(hipMemcpyAsync(I->ctl, &c0, sizeof(c0), hipMemcpyHostToDevice, st));
-  HIPCHK(hipMemsetAsync(I->bar, 0, I->bar_bytes, st));
   HIPCHK(launch_fill(I->V.warm, I->n_warm, NAN, st));
   KArgs a{};
   a.P = I->P;
   a.V = I->V;
   a.S = h->ds;
   a.ctl = I->ctl;
-  a.bar = I->bar;
+  a.comm.abort = (int*)I->comm;
+  a.comm.out = I->comm + COMM_HEAD;
+  a.comm.in = a.comm.out + 2 * SL_COUNT * COMM_COPIES;
   a.T = I->T;
   a.spin_limit = h->spin_limit;
   a.qmax = I->qmax;
@@ -1490,11 +1489,21 @@ int pdhcg_solve(pdhcg_handle* h, const double* x0, const double* y0, pdhcg_resul
   }
   while (true) {
     a.stop_at = std::min<long long>(maxit, c.ktot + h->s.host_poll);
+    // the exchange words are told apart by their epoch, which goes on from
+    // launch to launch; they are cleared before the first one, after an
+    // aborted launch and long before the epoch could wrap
+    if (I->epoch == 0 || I->epoch >= 1u << 31) {
+      HIPCHK(hipMemsetAsync(I->comm, 0, I->comm_bytes, st));
+      I->epoch = 0;
+    }
+    a.epoch = I->epoch;
+    I->epoch = 0;
     if (timing) HIPCHK(hipEventRecord(ev0, st));
     HIPCHK(launch_solve(a, phase32, I->grid, st));
     if (timing) HIPCHK(hipEventRecord(ev1, st));
     HIPCHK(hipMemcpyAsync(&c, I->ctl, sizeof(c), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
+    if (c.status != PDHCG_ABORTED) I->epoch = c.epoch;
     ++nlaunch;
     if (timing) {
       float ms = 0.0f;

@@ -12,7 +12,7 @@ constexpr int MAX_BLOCK = 1024;
 // per-coordinate kind used by elementwise passes
 enum : uint8_t { CT_FREE = 0, CT_NONNEG = 1, CT_CONE = 2, CT_BOX = 3 };
 
-// reduction slots (each slot holds one double per workgroup)
+// reduction slots (one double per workgroup, summed over the team)
 enum Slot : int {
   SL_DELTA2 = 0,   // ||u_new - u||^2                (inner stop test)
   SL_SJS,          // <s, J s>                       (BB numerator)
@@ -97,7 +97,6 @@ struct DevVec {
   double *t1, *t2;               // SpMV results of the current pass (n)
   double *warm;                  // root-finding warm starts, 2 x (n_wave + n_lane)
   double *xb, *yb, *Axb;         // averaged scheme
-  double *partials;              // SL_COUNT x G
 };
 
 struct DevSettings {
@@ -124,7 +123,7 @@ struct Ctl {
   int status;       // 0 running, else PDHCG_* status
   int started;
   int resume;       // with started = 0: re-initialise from zb / y, keep counters
-  int pad1;
+  unsigned epoch;   // grid all-reduces done on the handle's exchange words
   double hx[RMAX];  // R^ x of the current Halpern primal state
   double hxb[RMAX]; // R^ xbar (averaged scheme)
   unsigned long long pt[16];  // phase timers (wall-clock ticks, workgroup 0)
@@ -140,14 +139,16 @@ struct TraceBufs {
   double *sc;                    // cap * 8 scalars
 };
 
-// grid barrier state: one arrival word per workgroup (64-byte stride) and a
-// release word written by workgroup 0
-constexpr int BAR_STRIDE = 16;
-struct Barrier {
-  unsigned gen;
-  int abort;
-  unsigned pad[BAR_STRIDE - 2];
-  unsigned arrive[1];   // really [G * BAR_STRIDE]
+// what the workgroups of a grid exchange (one allocation): the abort word, one
+// pair of words per slot and workgroup for its partial, and COMM_COPIES
+// copies of one pair per slot for the totals.  A pair carries the two halves
+// of a double, each beside the epoch of the all-reduce that wrote it.
+constexpr int COMM_COPIES = 4;
+constexpr int COMM_HEAD = 16;        // words before the totals (the abort word's line)
+struct Comm {
+  int* abort;
+  unsigned long long* in;    // [SL_COUNT][G][2]
+  unsigned long long* out;   // [COMM_COPIES][SL_COUNT][2]
 };
 
 struct KArgs {
@@ -155,10 +156,11 @@ struct KArgs {
   DevVec V;
   DevSettings S;
   Ctl* ctl;
-  Barrier* bar;
+  Comm comm;
+  unsigned epoch;      // all-reduces done on these words before this launch
   TraceBufs T;
   long long stop_at;   // return to the host when ktot reaches this
-  unsigned long long spin_limit;  // grid-barrier wait bound, wall-clock ticks
+  unsigned long long spin_limit;  // all-reduce wait bound, wall-clock ticks
   double qmax;         // max_i diag(Q^)_i (first Euclidean BB step)
   int lds_bytes;       // dynamic LDS per workgroup (R slice; 0 = none)
   int profile;         // accumulate phase timers in ctl->pt and ptimes
