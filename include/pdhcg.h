@@ -71,7 +71,7 @@ extern "C" {
 #define PDHCG_MAX_ITER    2
 #define PDHCG_TIME_LIMIT  3
 #define PDHCG_NUMERICAL   4   /* NaN/Inf detected in the iterates            */
-#define PDHCG_ABORTED     5   /* device-side grid barrier timed out          */
+#define PDHCG_ABORTED     5   /* device-side all-reduce timed out            */
 
 /* ---- cone types ------------------------------------------------------- */
 #define PDHCG_CONE_FREE   0
@@ -376,13 +376,10 @@ int pdhcg_project_cones(int32_t type, int32_t dim, int64_t count, const double* 
  * asynchronously on `stream` (hipStream_t as void*, NULL = null stream), no
  * allocation, no memset and no host synchronisation.  r, out: count*dim
  * doubles; metric: count*dim or NULL; alpha: count (POW) -- all device
- * memory owned by the caller.  The per-block flags (metric constant on the
- * block) go to a static device array of the library, one per device, held
- * until the process ends: count may not exceed 4,194,304 blocks
- * (PDHCG_E_ARG otherwise).  Every call on a device writes that device's
- * array, so calls that overlap on one device (different streams, threads)
- * race; serialise them.  Metric and alpha values are not checked (invalid
- * ones give NaN).  Errors: PDHCG_E_ARG, PDHCG_E_CONE, PDHCG_E_HIP.         */
+ * memory owned by the caller.  count may not exceed 4,194,304 blocks
+ * (PDHCG_E_ARG otherwise).  Calls share no state of the library: they may
+ * overlap on streams and threads.  Metric and alpha values are not checked
+ * (invalid ones give NaN).  Errors: PDHCG_E_ARG, PDHCG_E_CONE, PDHCG_E_HIP. */
 int pdhcg_project_cones_noalloc(int32_t type, int32_t dim, int64_t count, const double* alpha,
                                 const double* r, const double* metric, double* out, void* stream);
 

@@ -1735,19 +1735,9 @@ int pdhcg_project_cones(int32_t type, int32_t dim, int64_t count, const double* 
   if (count == 0) return PDHCG_OK;
   if (!r || !out || (type == PDHCG_CONE_POW && !alpha)) return PDHCG_E_ARG;
   const size_t len = (size_t)count * (size_t)dim;
-  std::vector<unsigned char> eu((size_t)count, 1);
-  if (metric) {
+  if (metric)
     for (size_t i = 0; i < len; ++i)
       if (!(metric[i] > 0.0) || !std::isfinite(metric[i])) return PDHCG_E_ARG;
-    // a metric that is constant on a block takes the Euclidean formula, as in
-    // the solver (Pi^{cI} = Pi^I)
-    for (int64_t b = 0; b < count; ++b) {
-      const double* mb = metric + (size_t)b * dim;
-      bool c = true;
-      for (int j = 1; j < dim; ++j) c = c && (mb[j] == mb[0]);
-      eu[(size_t)b] = c ? 1 : 0;
-    }
-  }
   if (type == PDHCG_CONE_POW)
     for (int64_t b = 0; b < count; ++b)
       if (!(alpha[b] > 0.0 && alpha[b] < 1.0)) return PDHCG_E_CONE;
@@ -1756,7 +1746,6 @@ int pdhcg_project_cones(int32_t type, int32_t dim, int64_t count, const double* 
   double* d_o = B.alloc<double>(len);
   double* d_m = metric ? B.alloc<double>(len) : nullptr;
   double* d_a = type == PDHCG_CONE_POW ? B.alloc<double>((size_t)count) : nullptr;
-  unsigned char* d_e = B.alloc<unsigned char>((size_t)count);
   if (B.err != hipSuccess) {
     B.release();
     return PDHCG_E_MEM;
@@ -1764,8 +1753,7 @@ int pdhcg_project_cones(int32_t type, int32_t dim, int64_t count, const double* 
   hipError_t e = hipMemcpy(d_r, r, len * sizeof(double), hipMemcpyHostToDevice);
   if (e == hipSuccess && d_m) e = hipMemcpy(d_m, metric, len * sizeof(double), hipMemcpyHostToDevice);
   if (e == hipSuccess && d_a) e = hipMemcpy(d_a, alpha, (size_t)count * sizeof(double), hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemcpy(d_e, eu.data(), (size_t)count, hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = launch_project(type, dim, (long)count, d_a, d_r, d_m, d_e, d_o, nullptr);
+  if (e == hipSuccess) e = launch_project(type, dim, (long)count, d_a, d_r, d_m, d_o, nullptr);
   if (e == hipSuccess) e = hipMemcpy(out, d_o, len * sizeof(double), hipMemcpyDeviceToHost);
   B.release();
   return e == hipSuccess ? PDHCG_OK : PDHCG_E_HIP;

@@ -38,7 +38,7 @@ hipError_t read_cone_failure(double rec[8], unsigned* count);
 
 // diagnostic projection of `count` blocks of one cone type (device buffers)
 hipError_t launch_project(int type, int dim, long count, const double* alpha, const double* r,
-                          const double* m, const unsigned char* euclid, double* out, hipStream_t st);
+                          const double* m, double* out, hipStream_t st);
 
 // batch solve (one workgroup per instance)
 int batch_grid_limit(bool cones, bool ext);
