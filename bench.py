@@ -57,7 +57,7 @@ MEASURED_TRAFFIC = {
     # (degree coordinate order)
     "bytes_per_launch": 7783200183547.8,
 }
-KERNEL_SOURCES = ("solver.hip", "cones.hpp", "common.hpp", "api.cpp", "host_setup.cpp")
+KERNEL_SOURCES = ("solver.hip", "resident.hpp", "cones.hpp", "common.hpp", "api.cpp", "host_setup.cpp")
 
 
 def kernel_sources_hash():
@@ -451,13 +451,19 @@ def timed_solves(prob, args, budget, precision="fp64", verbose=0):
 
 def solver_kernel_name(prob, precision, grid):
     """The library's solver kernel for this solve: FP32 bulk, one workgroup,
-    the implementation-form features (row bounds, boxes, fixed-middle EXP),
-    or, without cone blocks, the cone-free kernel at two workgroups per CU."""
+    the register-resident core, the implementation-form features (row
+    bounds, boxes, fixed-middle EXP), or, without cone blocks, the cone-free kernel at two workgroups per CU."""
     kinds = {k for k, _, _, _ in prob.cones}
     ext = getattr(prob, "row_lo", None) is not None or bool(kinds & {"box", "exp1"})
     cones = bool(kinds & {"soc", "rsoc", "exp", "pow", "exp1"})
     if precision == "fp32":
         return "solve_kernel_f32" + ("" if cones else "_lin") + ("_ext" if ext else "")
+    # register-resident core: at most 512 coordinates and rows on one
+    # workgroup, about 1,024 of each a workgroup on a grid
+    if grid == 1 and max(prob.n, prob.m) <= 512:
+        return "resident_kernel_one"
+    if grid > 1 and max(prob.n, prob.m) <= 900 * grid:
+        return "resident_kernel"
     if grid == 1:
         return "solve_kernel_one_ext" if ext else "solve_kernel_one"
     if ext:

@@ -148,9 +148,12 @@ struct Batch {
   double* d_s = nullptr;          // packed dual slacks (host outputs), made on first use
   double* io = nullptr;           // IO_DOUBLES of scratch for the dual-slack output
   std::vector<long> offx, offy;   // count + 1 prefix sums of n and m
-  int grid = 1;
-  bool cones = false;             // some instance has SOC/RSOC/EXP/POW blocks
-  bool ext = false;               // some instance has row bounds, boxes or EXP1 blocks
+  int grid = 1, grid_res = 0;
+  int nres = 0;                   // instances of the register-resident core (first in the queue order)
+  int lds_res = 0;                // the dynamic LDS they need
+  bool cones_res = false;         // some of them has SOC/RSOC/EXP/POW blocks
+  bool cones = false;             // some other instance has
+  bool ext = false;               // some other instance has row bounds, boxes or EXP1 blocks
   int div_a = 2, div_at = 2;      // lanes-per-row rule: lanes <= mean nnz / div
   double tune_s = 0.0;
   hipStream_t cap = nullptr;      // private stream used for graph capture
@@ -219,6 +222,77 @@ DevSettings to_dev(const pdhcg_settings& s) {
   d.pid_kd = s.pid_kd;
   d.trace_iters = s.trace_iters;
   return d;
+}
+
+// ---- the register-resident core (resident.hpp): which problems it takes
+bool res_settings(const Handle* h, const HostInstance& H) {
+  return h->s.precision == PDHCG_PREC_FP64 && h->s.scheme == PDHCG_SCHEME_RH && !H.resc && H.n > 0;
+}
+
+// rows of [a, b) longer than RES_LONG
+int long_rows(const Csr& M, long a, long b) {
+  int k = 0;
+  for (long i = a; i < b; ++i) k += M.ptr[i + 1] - M.ptr[i] > RES_LONG ? 1 : 0;
+  return k;
+}
+
+long res_chunk(long nnz) {
+  return std::min<long>(RES_CHUNK_MAX, std::max<long>(block_size(), (nnz + block_size() - 1) / block_size() * block_size()));
+}
+
+bool sparse_q(const HostInstance& H) { return H.P.rows > 0 && !H.p_diag && !H.q_diag; }
+
+// a problem on one workgroup with at most one coordinate and one row a thread
+// (512 of each): the LDS it needs and whether the columns of R fit in it too.
+// Four coordinates a thread do not fit the 256 registers beside the vectors
+// (1,000 portfolios of 50 to 2,000 assets: 25 ms, 22 ms in the general core).
+// The rule looks at the instance alone, so an instance solved alone and in a
+// batch takes the same core.
+int res_one(const Handle* h, const HostInstance& H, DevProblem& P) {
+  P.res = RES_NONE;
+  const long bs = block_size();
+  if (!res_settings(h, H) || H.n > bs || H.m > bs) return 0;
+  const long nz = std::max<long>(H.A.nnz(), sparse_q(H) ? H.P.nnz() : 0);
+  if (long_rows(H.A, 0, H.m) > RES_LMAX || long_rows(H.AT, 0, H.n) > RES_LMAX ||
+      (sparse_q(H) && long_rows(H.P, 0, H.n) > RES_LMAX))
+    return 0;
+  const long chunk = res_chunk(nz);
+  if (res_lds_bytes(H.n, H.m, H.r, false, chunk, true, true) > RES_LDS_DYN) return 0;
+  P.res = RES_ONE;
+  P.res_chunk = (int)chunk;
+  P.res_r_lds = res_lds_bytes(H.n, H.m, H.r, true, chunk, true, true) <= RES_LDS_DYN ? 1 : 0;
+  return (int)res_lds_bytes(H.n, H.m, H.r, P.res_r_lds != 0, chunk, true, true);
+}
+
+// a partition whose every workgroup fits (one coordinate and row a thread, or
+// two of each): the LDS of the largest one, 0 when some workgroup does not fit
+int res_grid(const HostInstance& H, const std::vector<long>& pc, const std::vector<long>& pr, bool cones,
+             DevProblem& P) {
+  const int G = (int)pc.size() - 1;
+  const long cap = 2L * block_size();
+  const bool sp = sparse_q(H);
+  long nz = 0, most = 0;
+  P.res = RES_NONE;
+  for (int w = 0; w < G; ++w) {
+    most = std::max(most, std::max(pc[w + 1] - pc[w], pr[w + 1] - pr[w]));
+    if (pc[w + 1] - pc[w] > cap || pr[w + 1] - pr[w] > cap) return 0;
+    nz = std::max(nz, H.A.ptr[pr[w + 1]] - H.A.ptr[pr[w]]);
+    nz = std::max(nz, H.AT.ptr[pc[w + 1]] - H.AT.ptr[pc[w]]);
+    if (sp) nz = std::max(nz, H.P.ptr[pc[w + 1]] - H.P.ptr[pc[w]]);
+    if (long_rows(H.A, pr[w], pr[w + 1]) > RES_LMAX || long_rows(H.AT, pc[w], pc[w + 1]) > RES_LMAX ||
+        (sp && long_rows(H.P, pc[w], pc[w + 1]) > RES_LMAX))
+      return 0;
+  }
+  const long chunk = res_chunk(nz);
+  size_t lds[2] = {0, 0};
+  for (int w = 0; w < G; ++w)
+    for (int rl = 0; rl < 2; ++rl)
+      lds[rl] = std::max(lds[rl], res_lds_bytes(pc[w + 1] - pc[w], pr[w + 1] - pr[w], H.r, rl != 0, chunk, cones, false));
+  if (lds[0] > RES_LDS_DYN) return 0;
+  P.res = most <= block_size() ? RES_GRID1 : RES_GRID2;
+  P.res_chunk = (int)chunk;
+  P.res_r_lds = H.r > 0 && lds[1] <= RES_LDS_DYN ? 1 : 0;
+  return (int)lds[P.res_r_lds];
 }
 
 int upload_instance(Handle* h, Instance* I) {
@@ -339,24 +413,31 @@ int upload_instance(Handle* h, Instance* I) {
   bool lin_kernel = false;    // the solve runs solve_kernel_lin(_ext) (set with the grid)
   int maxg = 1;
   HIPCHK(max_resident_grid_for(fp32, P.ext != 0, has_cones, 0, &maxg));
-  int G = h->s.grid_dim;
-  if (G <= 0) {
-    long work = std::max<long>(std::max<long>(n, m), 1);
-    // about two thirds of a workgroup's threads per row or coordinate
-    // (measured: more, smaller workgroups shorten every latency-bound phase)
-    const long per = std::max(1L, (long)block_size() * 2 / 3);
-    long want = (work + per - 1) / per;
-    G = (int)std::min<long>(std::max<long>(want, 1), maxg);
+  auto grid_for = [&](int limit) {
+    long want = h->s.grid_dim;
+    if (want <= 0) {
+      const long work = std::max<long>(std::max<long>(n, m), 1);
+      // about two thirds of a workgroup's threads per row or coordinate
+      // (measured: more, smaller workgroups shorten every latency-bound phase)
+      const long per = std::max(1L, (long)block_size() * 2 / 3);
+      want = (work + per - 1) / per;
+    }
+    return (int)std::max<long>(1, std::min<long>(want, limit));
+  };
+  int G = grid_for(maxg);
+  // the register-resident core: one workgroup per CU
+  int res_g = 0;
+  if (G == 1) {
+    I->lds_bytes = res_one(h, H, P);
+  } else if (res_settings(h, H)) {
+    HIPCHK(max_resident_grid_res(has_cones, (int)RES_LDS_DYN, &res_g));
+    if (res_g > 1) G = grid_for(res_g);
   }
-  G = std::max(1, std::min(G, maxg));
-  I->grid = G;
-  lin_kernel = !has_cones && G > 1;
   // ownership ranges: coordinates weighted by their share of the A^T and P
   // passes, the dense factor and the cone projections (cone blocks are never
   // split); rows by their nonzeros
   {
-    std::vector<long> pc(G + 1, 0), pr(G + 1, 0);
-    std::vector<int> pw(G + 1, 0), pl(G + 1, 0);
+    std::vector<long> pc, pr;
     // split into G contiguous ranges.  A unit flagged heavy (it holds a row
     // far longer than the rest) gets a workgroup of its own, so its lanes are
     // chosen for it alone; the other workgroups are shared among the light
@@ -490,13 +571,11 @@ int upload_instance(Handle* h, Instance* I) {
       out[G] = total_items;
     };
     std::vector<std::pair<long, double>> cu;
-    std::vector<char> cheavy;
     // unit kinds: elementwise coordinates, or the cone type; a workgroup's
     // range never spans two kinds, so no workgroup runs two kinds of
     // projection (or mixes SOC and RSOC group widths) one after the other
     std::vector<signed char> ckind;
     cu.reserve(n);
-    cheavy.reserve(n);
     ckind.reserve(n);
     // heavy: a unit with an A^T or P row of at least 4096 nonzeros and over
     // half a workgroup's share of the total weight (flags set below, once
@@ -570,12 +649,6 @@ int upload_instance(Handle* h, Instance* I) {
         ckind.push_back((signed char)(1 + cb.type));
       }
     }
-    {
-      double wtot = 0.0;
-      for (const auto& u : cu) wtot += u.second;
-      const double heavy_nz = std::max(4096.0, 0.5 * wtot / G);
-      for (double z : unit_nz) cheavy.push_back(z > heavy_nz);
-    }
     // with many alternating kinds the kind boundaries would fragment the
     // split: keep them only while there are few kind runs
     auto few_runs = [&](std::vector<signed char>& kind) {
@@ -583,8 +656,6 @@ int upload_instance(Handle* h, Instance* I) {
       for (size_t i = 0; i < kind.size(); ++i) runs += (i == 0 || kind[i] != kind[i - 1]) ? 1 : 0;
       if (runs > std::max(1, G / 8)) std::fill(kind.begin(), kind.end(), (signed char)0);
     };
-    few_runs(ckind);
-    split(cu, cheavy, ckind, n, pc);
     // rows: weighted by their nonzeros; a workgroup's rows share one length
     // class (<= 16, 64, 256, 1024 nonzeros, longer) while the classes come in
     // few runs, so the lanes per row chosen from the mean fit every row
@@ -596,8 +667,32 @@ int upload_instance(Handle* h, Instance* I) {
       ru.emplace_back(l + 1, 2.0 + (double)z);
       rkind[l] = (signed char)(z <= 16 ? 0 : (z <= 64 ? 1 : (z <= 256 ? 2 : (z <= 1024 ? 3 : 4))));
     }
-    few_runs(rkind);
-    split(ru, std::vector<char>(ru.size(), 0), rkind, m, pr);
+    auto partition = [&]() {
+      double wtot = 0.0;
+      for (const auto& u : cu) wtot += u.second;
+      const double heavy_nz = std::max(4096.0, 0.5 * wtot / G);
+      std::vector<char> cheavy;
+      cheavy.reserve(unit_nz.size());
+      for (double z : unit_nz) cheavy.push_back(z > heavy_nz);
+      std::vector<signed char> ck = ckind, rk = rkind;
+      few_runs(ck);
+      few_runs(rk);
+      pc.assign(G + 1, 0);
+      pr.assign(G + 1, 0);
+      split(cu, cheavy, ck, n, pc);
+      split(ru, std::vector<char>(ru.size(), 0), rk, m, pr);
+    };
+    partition();
+    if (G > 1 && res_g > 1) {
+      I->lds_bytes = res_grid(H, pc, pr, has_cones, P);
+      if (I->lds_bytes == 0 && grid_for(maxg) != G) {
+        G = grid_for(maxg);
+        partition();
+      }
+    }
+    I->grid = G;
+    lin_kernel = !has_cones && G > 1;
+    std::vector<int> pw(G + 1, 0), pl(G + 1, 0);
     for (int w = 0; w <= G; ++w) {
       pw[w] = (int)(std::lower_bound(H.wave_start.begin(), H.wave_start.end(), (int)std::min<long>(pc[w], n)) -
                     H.wave_start.begin());
@@ -656,15 +751,50 @@ int upload_instance(Handle* h, Instance* I) {
       lanes[4 * w + 2] = (unsigned short)(maxdim <= 17 ? 16 : (maxdim <= 33 ? 32 : 64));
     }
     // the owned columns of R in LDS when the largest slice fits in 64 KiB
-    long maxloc = 0;
-    for (int w = 0; w < G; ++w) maxloc = std::max(maxloc, pc[w + 1] - pc[w]);
-    const size_t rbytes = (size_t)H.r * (size_t)maxloc * sizeof(double);
-    I->lds_bytes = (H.r > 0 && rbytes <= (size_t)64 * 1024) ? (int)rbytes : 0;
-    if (I->lds_bytes > 0) {
-      // the slice must not cost the grid its residency
-      int mg = 0;
-      HIPCHK(max_resident_grid_for(fp32, P.ext != 0, has_cones, I->lds_bytes, &mg));
-      if (mg < G) I->lds_bytes = 0;
+    if (P.res == RES_NONE) {
+      long maxloc = 0;
+      for (int w = 0; w < G; ++w) maxloc = std::max(maxloc, pc[w + 1] - pc[w]);
+      const size_t rbytes = (size_t)H.r * (size_t)maxloc * sizeof(double);
+      I->lds_bytes = (H.r > 0 && rbytes <= (size_t)64 * 1024) ? (int)rbytes : 0;
+      if (I->lds_bytes > 0) {
+        // the slice must not cost the grid its residency
+        int mg = 0;
+        HIPCHK(max_resident_grid_for(fp32, P.ext != 0, has_cones, I->lds_bytes, &mg));
+        if (mg < G) I->lds_bytes = 0;
+      }
+    }
+    if (P.res != RES_NONE && G > 1) {
+      // the gathered vectors travel in ring buffers in which every
+      // workgroup's part starts a line of its own; the products read them
+      // through column indices that are positions there
+      auto place = [&](const std::vector<long>& cut, long total, std::vector<long>& pad, std::vector<int>& pos) {
+        pad.assign(G + 1, 0);
+        pos.resize(std::max<long>(total, 1));
+        for (int w = 0; w < G; ++w) {
+          for (long i = cut[w]; i < cut[w + 1]; ++i) pos[i] = (int)(pad[w] + i - cut[w]);
+          pad[w + 1] = (pad[w] + cut[w + 1] - cut[w] + RES_RING_ALIGN - 1) / RES_RING_ALIGN * RES_RING_ALIGN;
+        }
+        return std::max<long>(pad[G], RES_RING_ALIGN);
+      };
+      std::vector<long> padc, padr;
+      std::vector<int> posc, posr;
+      V.ld_n = place(pc, n, padc, posc);
+      V.ld_m = place(pr, m, padr, posr);
+      auto through = [&](const std::vector<int32_t>& col, const std::vector<int>& pos) {
+        std::vector<int> x(col.size());
+        for (size_t k = 0; k < col.size(); ++k) x[k] = pos[col[k]];
+        return B.upload(x);
+      };
+      P.A_colx = through(H.A.col, posc);
+      P.AT_colx = through(H.AT.col, posr);
+      P.P_colx = sparse_p ? through(H.P.col, posc) : nullptr;
+      P.pad_c = B.upload(padc);
+      P.pad_r = B.upload(padr);
+      // up to 2 MB of buffers (a share of an XCD's L2 beside the matrices),
+      // at least two: a buffer is filled while its predecessor is read
+      V.nring = (int)std::min<long>(16, std::max<long>(2, (2L << 20) / (8 * (V.ld_n + V.ld_m))));
+      V.ring_n = B.alloc<double>((size_t)V.nring * V.ld_n);
+      V.ring_m = B.alloc<double>((size_t)V.nring * V.ld_m);
     }
     // skewed A^T row lengths (some row of a workgroup more than 16 times its
     // mean and longer than 64): order each workgroup's rows by length class
@@ -1070,6 +1200,26 @@ BatchArgs batch_args(Handle* h, long long stop_at) {
   return a;
 }
 
+// the instances of the register-resident core, then the others, each with a
+// queue of its own
+hipError_t launch_batches(Handle* h, long long stop_at, unsigned long long* ptimes, hipStream_t st) {
+  Batch* B = h->B;
+  BatchArgs a = batch_args(h, stop_at);
+  a.ptimes = ptimes;
+  hipError_t e = hipSuccess;
+  if (B->nres > 0) {
+    a.count = B->nres;
+    e = launch_batch(a, true, B->cones_res, false, B->lds_res, B->grid_res, st);
+  }
+  if (e == hipSuccess && B->nres < B->count) {
+    a.first = B->nres;
+    a.count = B->count;
+    a.queue = B->d_queue + 1;
+    e = launch_batch(a, false, B->cones, B->ext, 0, B->grid, st);
+  }
+  return e;
+}
+
 int setup_batch(Handle* h) {
   Batch* B = h->B;
   const int count = B->count;
@@ -1117,7 +1267,7 @@ int setup_batch(Handle* h) {
   // control blocks, queue, order (largest first), packed outputs
   B->d_ctl = B->mem.alloc<Ctl>(count);
   B->d_desc = B->mem.alloc<InstDesc>(count);
-  B->d_queue = B->mem.alloc<int>(1);
+  B->d_queue = B->mem.alloc<int>(2);
   B->d_norm = B->mem.alloc<double>(count);
   B->offx.assign(count + 1, 0);
   B->offy.assign(count + 1, 0);
@@ -1138,17 +1288,29 @@ int setup_batch(Handle* h) {
     work[i] = (double)H.n * (4.0 + H.r) + 2.0 * (double)H.A.nnz() + (double)H.P.nnz() +
               32.0 * (double)(H.wave_start.size() + H.lane_start.size());
   }
-  std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return work[a] > work[b]; });
+  for (int i = 0; i < count; ++i) B->lds_res = std::max(B->lds_res, res_one(h, h->inst[i]->H, B->desc[i].P));
+  auto general = [&](int i) { return B->desc[i].P.res == RES_NONE; };
+  std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
+    return general(a) != general(b) ? general(b) : work[a] > work[b];
+  });
   B->d_order = B->mem.upload(order);
   if (B->mem.err != hipSuccess) return B->mem.err == hipErrorOutOfMemory ? PDHCG_E_MEM : PDHCG_E_HIP;
   for (int i = 0; i < count; ++i) {
     const HostInstance& H = h->inst[i]->H;
-    if (!H.wave_start.empty() || !H.lane_start.empty()) B->cones = true;
-    if (needs_ext(H)) B->ext = true;
+    const bool cones = !H.wave_start.empty() || !H.lane_start.empty();
+    if (!general(i)) {
+      B->nres += 1;
+      B->cones_res = B->cones_res || cones;
+      continue;
+    }
+    B->cones = B->cones || cones;
+    B->ext = B->ext || needs_ext(H);
   }
-  const int lim = batch_grid_limit(B->cones, B->ext);
-  B->grid = h->s.grid_dim > 0 ? std::min(h->s.grid_dim, lim) : lim;
-  B->grid = std::max(1, std::min(B->grid, count));
+  auto grid_of = [&](int lim, int k) {
+    return std::max(1, std::min(h->s.grid_dim > 0 ? std::min(h->s.grid_dim, lim) : lim, k));
+  };
+  if (B->nres > 0) B->grid_res = grid_of(batch_grid_limit(true, B->cones_res, false, B->lds_res), B->nres);
+  B->grid = B->nres < count ? grid_of(batch_grid_limit(false, B->cones, B->ext, 0), count - B->nres) : B->grid_res;
 
   // step sizes: power iteration per instance with the default lane rule
   set_lanes(h, 0, 0);
@@ -1175,7 +1337,7 @@ int setup_batch(Handle* h) {
   }
   // autotuner: time a fixed number of outer iterations of the whole batch
   // under each candidate lanes-per-row rule and keep the fastest
-  if (h->s.autotune && h->s.lanes_a <= 0 && h->s.lanes_at <= 0) {
+  if (h->s.autotune && h->s.lanes_a <= 0 && h->s.lanes_at <= 0 && B->nres < count) {
     const double t0 = now_s();
     const int it = h->s.tune_iters > 0 ? h->s.tune_iters : 64;
     hipEvent_t e0, e1;
@@ -1193,7 +1355,7 @@ int setup_batch(Handle* h) {
           if (rc != PDHCG_OK) return rc;
           HIPCHK(launch_batch_reset(B->d_desc, count, B->d_queue, st));
           HIPCHK(hipEventRecord(e0, st));
-          HIPCHK(launch_batch(batch_args(h, it), B->cones, B->ext, B->grid, st));
+          HIPCHK(launch_batches(h, it, nullptr, st));
           HIPCHK(hipEventRecord(e1, st));
           HIPCHK(hipEventSynchronize(e1));
           float ms = 0.0f;
@@ -1228,7 +1390,7 @@ int capture_batch(Handle* h) {
   if (!B->cap) HIPCHK(hipStreamCreateWithFlags(&B->cap, hipStreamNonBlocking));
   HIPCHK(hipStreamBeginCapture(B->cap, hipStreamCaptureModeThreadLocal));
   hipError_t e = launch_batch_reset(B->d_desc, B->count, B->d_queue, B->cap);
-  if (e == hipSuccess) e = launch_batch(batch_args(h, h->s.max_iter), B->cones, B->ext, B->grid, B->cap);
+  if (e == hipSuccess) e = launch_batches(h, h->s.max_iter, nullptr, B->cap);
   if (e == hipSuccess)
     e = launch_batch_gather(B->d_desc, B->count, B->d_offx, B->d_offy, B->d_outx, B->d_outy,
                             h->s.scheme == PDHCG_SCHEME_AVG ? 1 : 0, B->cap);
@@ -1640,14 +1802,14 @@ int pdhcg_solve_batch(pdhcg_handle* h, const double* const* x0s, const double* c
   unsigned long long* dpt = nullptr;
   DevBuf tbuf;                  // phase timers (settings.verbose & 8)
   tbuf.use(h->s);
+  const int pgrid = std::max(B->grid, B->grid_res);
   if (h->s.verbose & 8) {
     // profiled run: a direct launch with phase timers instead of the graph
-    dpt = tbuf.alloc<unsigned long long>((size_t)PT_COUNT * B->grid);
+    dpt = tbuf.alloc<unsigned long long>((size_t)PT_COUNT * pgrid);
     if (tbuf.err != hipSuccess) return PDHCG_E_MEM;
-    BatchArgs pa = batch_args(h, h->s.max_iter);
-    pa.ptimes = dpt;
+    HIPCHK(hipMemsetAsync(dpt, 0, sizeof(unsigned long long) * PT_COUNT * pgrid, st));
     HIPCHK(launch_batch_reset(B->d_desc, B->count, B->d_queue, st));
-    HIPCHK(launch_batch(pa, B->cones, B->ext, B->grid, st));
+    HIPCHK(launch_batches(h, h->s.max_iter, dpt, st));
     HIPCHK(launch_batch_gather(B->d_desc, B->count, B->d_offx, B->d_offy, B->d_outx, B->d_outy,
                                h->s.scheme == PDHCG_SCHEME_AVG ? 1 : 0, st));
   } else {
@@ -1693,7 +1855,7 @@ int pdhcg_solve_batch(pdhcg_handle* h, const double* const* x0s, const double* c
     (void)hipEventDestroy(ev1);
   }
   if (dpt) {
-    report_phases(dpt, B->grid);
+    report_phases(dpt, pgrid);
     tbuf.release();
   }
   for (int i = 0; i < count; ++i) {

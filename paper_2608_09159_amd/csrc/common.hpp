@@ -83,10 +83,34 @@ struct DevProblem {
   // only; else null): at_perm[n], at_seg[(classes + 1) * G]
   const int* at_perm;
   const int* at_seg;
+  // register-resident core: its form, products staged at a time, whether the
+  // owned columns of R are staged; grids: column indices as positions in the
+  // ring buffers, and where each workgroup's part of them starts
+  int res, res_chunk, res_r_lds;
+  const int *A_colx, *AT_colx, *P_colx;
+  const long *pad_c, *pad_r;
   const unsigned short* part_lanes;  // per workgroup: lanes for A^T/P rows (up to
                                      // 512: the whole workgroup), A rows,
                                     // SOC/RSOC group width, pad
 };
+
+// the register-resident core (resident.hpp): which form runs a problem, and
+// what its workgroups need of LDS
+enum : int { RES_NONE = 0, RES_GRID1, RES_GRID2, RES_ONE };
+constexpr int RES_LONG = 32;          // rows longer than this are summed by a wave
+constexpr int RES_LMAX = 192;         // at most so many of them a workgroup and matrix
+constexpr int RES_CHUNK_MAX = 4096;   // products staged at a time
+constexpr int RES_LDS_STATIC = 32 * 1024;
+constexpr size_t RES_LDS_DYN = 160 * 1024 - RES_LDS_STATIC;
+constexpr int RES_RING_ALIGN = 32;    // doubles: a workgroup's part of a ring buffer starts a line
+
+// coordinates and rows of one workgroup, rank of R (0: its columns stay in
+// global memory), products staged; one: the whole problem on one workgroup
+constexpr size_t res_lds_bytes(long nl, long ml, int r, bool r_lds, long chunk, bool cones, bool one) {
+  const long prod = (r > 0 && nl > chunk) ? nl : chunk;
+  return sizeof(double) * (size_t)(prod + nl + (one ? ml : 0) + (cones ? 2 * nl : 0) + (nl > ml ? nl : ml) +
+                                   (r_lds ? (long)r * nl : 0));
+}
 
 struct DevVec {
   double *x, *y, *ax, *ay, *wx, *wy;
@@ -97,6 +121,9 @@ struct DevVec {
   double *t1, *t2;               // SpMV results of the current pass (n)
   double *warm;                  // root-finding warm starts, 2 x (n_wave + n_lane)
   double *xb, *yb, *Axb;         // averaged scheme
+  double *ring_n, *ring_m;       // register-resident grids: nring gather buffers of ld_n, ld_m
+  long ld_n, ld_m;
+  int nring;
 };
 
 struct DevSettings {
@@ -195,9 +222,9 @@ struct InstDesc {
 
 struct BatchArgs {
   const InstDesc* desc;
-  int count;
+  int first, count;        // queue positions [first, count) of this launch
   const int* order;        // queue position -> instance (largest first)
-  int* queue;              // next queue position (reset to 0 before a launch)
+  int* queue;              // positions taken (reset to 0 before a launch)
   DevSettings S;
   long long stop_at;       // per-instance iteration cap of this launch
   unsigned long long limit_ticks;   // per-launch wall-clock budget (0 = none)

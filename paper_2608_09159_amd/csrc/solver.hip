@@ -39,7 +39,6 @@
 #include <stdint.h>
 
 #include <algorithm>
-#include <mutex>
 #include <type_traits>
 
 #include "common.hpp"
@@ -54,13 +53,21 @@ constexpr int NWAVE = BLOCK / 64;
 constexpr int ITEM_CACHE = 256;   // cone items per kind cached in LDS
 constexpr int ZCAP = 1024;        // coordinates whose projection inputs/outputs can stage in LDS
 
+// the thread's index, opaque to the compiler: addresses and masks formed from
+// it are not loop invariants that it would keep in registers across the solve
+__device__ __forceinline__ int thread_here() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+
+// LDS of every solver core
 struct Lds {
-  double red[16][NWAVE];
+  double red[8][NWAVE];
   double scal[SL_COUNT];
   double mine[SL_COUNT];   // this workgroup's partials of the current all-reduce
   double ht[RMAX];       // D^ h for the Q product of the current pass
   double Dl[RMAX * RMAX];  // D^ (r x r), staged once per run
-  double hw[NWAVE][RMAX];   // per-wave R^ u accumulators (single-workgroup teams)
   double hu[RMAX];       // R^ u of the current inner iterate
   double hs[RMAX];       // R^ s, s = u - u_prev (one-sync inner step)
   // this workgroup's cone-item descriptors, copied once per launch when they
@@ -70,9 +77,6 @@ struct Lds {
   int lst[ITEM_CACHE];
   unsigned char ltype[ITEM_CACHE], leu[ITEM_CACHE];
   double lal[ITEM_CACHE];
-  // the inner step's cone-coordinate gradient and projected point, indexed
-  // from the workgroup's first coordinate (when it owns at most ZCAP)
-  double gl[ZCAP], zl[ZCAP];
   Ctl C;
   int flag;
   int done;
@@ -80,6 +84,14 @@ struct Lds {
   unsigned long long plast;
   unsigned epoch;
   unsigned long long pt[PT_COUNT];   // this workgroup's phase timers
+};
+
+// and of run_solver
+struct LdsGen : Lds {
+  double hw[NWAVE][RMAX];   // per-wave R^ u accumulators (single-workgroup teams)
+  // the inner step's cone-coordinate gradient and projected point, indexed
+  // from the workgroup's first coordinate (when it owns at most ZCAP)
+  double gl[ZCAP], zl[ZCAP];
 };
 
 // phase timer: charge the time since the last mark to the current category
@@ -156,7 +168,7 @@ struct SoloTeam {
 template <class SlotFn, class DstFn>
 __device__ __forceinline__ bool allreduce(const GridTeam& T, Lds& L, int ns, SlotFn slot_of, DstFn dst_of,
                                           bool acq) {
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int tid = thread_here(), lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int G = T.size, me = T.rank;
   __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this thread's stores are done
   if (tid == 0) {
@@ -221,27 +233,50 @@ __device__ __forceinline__ void acquire(const SoloTeam&) {}
 
 template <class SlotFn, class DstFn>
 __device__ __forceinline__ bool allreduce(const SoloTeam&, Lds& L, int ns, SlotFn slot_of, DstFn dst_of, bool) {
+  const int tid = thread_here();
   __syncthreads();
-  if ((int)threadIdx.x < ns) *dst_of(threadIdx.x) = L.mine[slot_of(threadIdx.x)];
+  if (tid < ns) *dst_of(tid) = L.mine[slot_of(tid)];
   __syncthreads();
   return true;
+}
+
+// a workgroup barrier for data in LDS alone: __syncthreads also waits for
+// every store to global memory, more than a microsecond for one that goes
+// through to memory
+__device__ __forceinline__ void lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 // ---------------------------------------------------------------------------
 // workgroup sums into L.mine
 // ---------------------------------------------------------------------------
-// sums of up to 16 per-thread values over the workgroup
-__device__ __forceinline__ void block_store(Lds& L, const double* v, const int* slots, int k) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+// up to eight slot indices in a word, the first lowest (an array indexed by
+// the thread would live in scratch memory, and its read back waits behind
+// every store in flight: more than a microsecond a sum)
+template <class... I>
+constexpr unsigned long long slot_list(I... i) {
+  unsigned long long w = 0;
+  int at = 0;
+  ((w |= (unsigned long long)i << at, at += 8), ...);
+  return w;
+}
+__device__ __forceinline__ int slot_at(unsigned long long slots, int q) { return (int)((slots >> (8 * q)) & 255); }
+static_assert(SL_COUNT <= 256, "slot indices in bytes");
+
+// sums of up to 8 per-thread values over the workgroup
+__device__ __forceinline__ void block_store(Lds& L, const double* v, unsigned long long slots, int k) {
+  const int tid = thread_here(), lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   for (int i = 0; i < k; ++i) {
     double s = wave_sum(v[i]);
     if (lane == 0) L.red[i][wv] = s;
   }
-  __syncthreads();
-  if ((int)threadIdx.x < k) {
+  lds_sync();
+  if (tid < k) {
     double s = 0.0;
-    for (int w = 0; w < NWAVE; ++w) s += L.red[threadIdx.x][w];
-    L.mine[slots[threadIdx.x]] = s;
+    for (int w = 0; w < NWAVE; ++w) s += L.red[tid][w];
+    L.mine[slot_at(slots, tid)] = s;
   }
 }
 
@@ -265,7 +300,7 @@ struct RSrc {
 // inside the coordinate passes: hw_clear, then hw_add per coordinate chunk
 // (one wave sum per factor row, into per-wave accumulators), then hw_store
 // sums the waves into L.mine.  Grids use hw_reduce_store below.
-__device__ __forceinline__ void hw_clear(Lds& L) {
+__device__ __forceinline__ void hw_clear(LdsGen& L) {
   for (int i = threadIdx.x; i < NWAVE * RMAX; i += BLOCK) (&L.hw[0][0])[i] = 0.0;
   __syncthreads();
 }
@@ -273,8 +308,8 @@ __device__ __forceinline__ void hw_clear(Lds& L) {
 // wave-uniform: add R[k, i] * val (0 if !active) to the wave's accumulators
 // (the product in the factor's precision, the sums in FP64)
 template <class MV>
-__device__ __forceinline__ void hw_add(Lds& L, const RSrc<MV>& R, int r, long i, double val, bool active) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+__device__ __forceinline__ void hw_add(LdsGen& L, const RSrc<MV>& R, int r, long i, double val, bool active) {
+  const int tid = thread_here(), lane = tid & 63, wv = tid >> 6;
   for (int k = 0; k < r; ++k) {
     double t = active ? (double)(R(k, i) * (MV)val) : 0.0;
     t = wave_sum(t);
@@ -282,7 +317,7 @@ __device__ __forceinline__ void hw_add(Lds& L, const RSrc<MV>& R, int r, long i,
   }
 }
 
-__device__ __forceinline__ void hw_store(Lds& L, int r) {
+__device__ __forceinline__ void hw_store(LdsGen& L, int r) {
   __syncthreads();
   if ((int)threadIdx.x < r) {
     double s = 0.0;
@@ -300,7 +335,7 @@ template <class MV>
 __device__ __forceinline__ void hw_reduce_store(Lds& L, const RSrc<MV>& R, int r, const double* v,
                                                 const double* vp, long c0, long c1) {
   __syncthreads();
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int tid = thread_here(), lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nsum = vp ? 2 * r : r;
   for (int q0 = wv; q0 < nsum; q0 += 3 * NWAVE) {
     int kk[3];
@@ -335,14 +370,14 @@ __device__ __forceinline__ double r_dot(const RSrc<MV>& R, int r, long i, const 
 // `k` scalar slots into L.scal and the r factor slots into dsth, in one
 // all-reduce (with neither, a barrier)
 template <class Team>
-__device__ __forceinline__ bool reduce_sh(const Team& T, Lds& L, const int* slots, int k, int r, double* dsth,
+__device__ __forceinline__ bool reduce_sh(const Team& T, Lds& L, unsigned long long slots, int k, int r, double* dsth,
                                           bool acq) {
   if (k + r == 0) {
     if (threadIdx.x == 0) L.mine[SL_NAN] = 0.0;
     return allreduce(T, L, 1, [](int) { return (int)SL_NAN; }, [&](int) { return &L.scal[SL_NAN]; }, acq);
   }
-  return allreduce(T, L, k + r, [&](int q) { return q < k ? slots[q] : (int)SL_H0 + q - k; },
-                   [&](int q) { return q < k ? &L.scal[slots[q]] : &dsth[q - k]; }, acq);
+  return allreduce(T, L, k + r, [&](int q) { return q < k ? slot_at(slots, q) : (int)SL_H0 + q - k; },
+                   [&](int q) { return q < k ? &L.scal[slot_at(slots, q)] : &dsth[q - k]; }, acq);
 }
 
 // after a projected step of the one-sync inner loop: ||s||^2, <s, M s>,
@@ -360,8 +395,8 @@ __device__ __forceinline__ bool reduce_step(const Team& T, Lds& L, int r, double
                   return q == 0 ? &L.scal[SL_DELTA2] : q == 1 ? &L.scal[SL_SJS] : q == 2 ? &L.scal[SL_SPS]
                        : q < 3 + r ? &L.hu[q - 3] : &L.hs[q - 3 - r];
                 }, false);
-  if (threadIdx.x < 64) {
-    const int a = threadIdx.x;
+  const int a = thread_here();
+  if (a < 64) {
     double t = 0.0;
     if (a < r) {
       double u = 0.0;
@@ -371,18 +406,24 @@ __device__ __forceinline__ bool reduce_step(const Team& T, Lds& L, int r, double
     t = wave_sum(t);
     if (a == 0) L.scal[SL_SDG] = L.scal[SL_SPS] + t + L.scal[SL_DELTA2] / tau;
   }
-  __syncthreads();
+  lds_sync();
   return ok;
 }
 
 // L.ht = D h
+__device__ __forceinline__ void times_d(Lds& L, const DevProblem& P, const double* h) {
+  const int a = thread_here();
+  if (a < P.r) {
+    double s = 0.0;
+    for (int b = 0; b < P.r; ++b) s += L.Dl[a * P.r + b] * h[b];
+    L.ht[a] = s;
+  }
+}
+
+// the same between barriers (global memory included)
 __device__ __forceinline__ void make_ht(Lds& L, const DevProblem& P, const double* h) {
   __syncthreads();
-  if ((int)threadIdx.x < P.r) {
-    double s = 0.0;
-    for (int b = 0; b < P.r; ++b) s += L.Dl[threadIdx.x * P.r + b] * h[b];
-    L.ht[threadIdx.x] = s;
-  }
+  times_d(L, P, h);
   __syncthreads();
 }
 
@@ -435,7 +476,7 @@ __device__ __forceinline__ void spmv_range(const int64_t* ptr, const int* col, c
     return;
   }
   const int groups = BLOCK / Lw;
-  const int gid = threadIdx.x / Lw, sub = threadIdx.x & (Lw - 1);
+  const int tid = thread_here(), gid = tid / Lw, sub = tid & (Lw - 1);
   for (long base = r0; base < r1; base += groups) {
     const long row = base + gid;
     const bool act = row < r1;
@@ -478,7 +519,7 @@ __device__ __noinline__ void spmv_classes(const int64_t* ptr, const int* col, co
 // wave-uniform loop over the coordinates [c0, c1): f(i, active)
 template <class F>
 __device__ __forceinline__ void for_range(long c0, long c1, F f) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int tid = thread_here(), lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   for (long base = c0 + (long)wv * 64; base < c1; base += BLOCK) {
     const long i = base + lane;
     f(i, i < c1);
@@ -489,7 +530,7 @@ __device__ __forceinline__ void for_range(long c0, long c1, F f) {
 template <class F>
 __device__ __forceinline__ void for_rows_range(long r0, long r1, int Lw, F f) {
   const int groups = BLOCK / Lw;
-  const int gid = threadIdx.x / Lw, sub = threadIdx.x & (Lw - 1);
+  const int tid = thread_here(), gid = tid / Lw, sub = tid & (Lw - 1);
   for (long base = r0; base < r1; base += groups) {
     const long row = base + gid;
     f(row, sub, row < r1);
@@ -520,6 +561,68 @@ __device__ __forceinline__ double dual_candidate(const DevProblem& P, long l, do
     }
   }
   return yl + sigma * (P.b[l] - axb);
+}
+
+// what one check decides from its reduced slots (thread 0)
+
+// residuals, objectives and status from SL_RP2, SL_RD2, SL_XQX, SL_CX, SL_BY
+// (and SL_BOXD)
+template <bool EXT>
+__device__ __forceinline__ void kkt_status(const DevProblem& P, const Run& A, Lds& L, bool bad) {
+  Ctl& C = L.C;
+  const double* sc = L.scal;
+  const double scale = P.nu_b * P.nu_c;
+  C.rel_p = sqrt(sc[SL_RP2]) / (1.0 + P.norm_b);
+  C.rel_d = sqrt(sc[SL_RD2]) / (1.0 + P.norm_c);
+  C.pobj = scale * (0.5 * sc[SL_XQX] + sc[SL_CX]);
+  if constexpr (EXT) {
+    C.dobj = scale * (sc[SL_BY] + sc[SL_BOXD] - 0.5 * sc[SL_XQX]);
+    // a fixed-middle EXP reduced cost with lambda_a < 0 = lambda_c has
+    // dual value -inf: no gap closure yet
+    C.rel_gap = C.dobj == -INFINITY ? 1.0 : fabs(C.pobj - C.dobj) / (1.0 + fabs(C.pobj) + fabs(C.dobj));
+  } else {
+    C.dobj = scale * (sc[SL_BY] - 0.5 * sc[SL_XQX]);
+    C.rel_gap = fabs(C.pobj - C.dobj) / (1.0 + fabs(C.pobj) + fabs(C.dobj));
+  }
+  if (bad || !isfinite(C.rel_p) || !isfinite(C.rel_d) || !isfinite(C.rel_gap)) {
+    C.status = PDHCG_NUMERICAL;
+  } else if (fmax(C.rel_p, fmax(C.rel_d, C.rel_gap)) <= A.S->tol) {
+    C.status = PDHCG_OPTIMAL;
+  } else if (A.deadline != 0ull && wall_clock64() > A.deadline) {
+    C.status = PDHCG_TIME_LIMIT;
+  }
+}
+
+// reflected Halpern: fixed-point error E, status, restart rule and primal
+// weight of the check at evaluation kt1 (the k-th of its epoch); whether to
+// restart
+template <bool EXT>
+__device__ __forceinline__ bool check_step(const DevProblem& P, const Run& A, Lds& L, long long k, long long kt1,
+                                           double omega, double& E) {
+  const DevSettings& S = *A.S;
+  Ctl& C = L.C;
+  const double* sc = L.scal;
+  const double E2 = omega * sc[SL_DX2] + sc[SL_DY2] / omega + 2.0 * P.eta * sc[SL_ADXDY];
+  E = sqrt(fmax(E2, 0.0));
+  bool rs = false;
+  if (k == 0) C.E0 = E;
+  else rs = (E <= S.beta_s * C.E0) || (E <= S.beta_n * C.E0 && E > C.Eprev) ||
+            ((double)(k + 1) >= S.beta_a * (double)kt1);
+  C.Eprev = E;
+  C.lastE = E;
+  kkt_status<EXT>(P, A, L, !isfinite(E));
+  if (C.status == 0 && rs) {
+    const double dxm = sqrt(sc[SL_MOVX2]), dym = sqrt(sc[SL_MOVY2]);
+    if (dxm > 1e-12 && dym > 1e-12) {
+      const double e = log_call(dym / (omega * dxm));
+      C.pid_I = S.pid_beta_i * C.pid_I + e;
+      C.omega = exp_call(log_call(omega) + S.pid_kp * e + S.pid_ki * C.pid_I + S.pid_kd * (e - C.e_prev));
+      C.e_prev = e;
+    }
+    C.k = 0;
+    C.restarts += 1;
+  }
+  return rs;
 }
 
 template <bool EXT>
@@ -696,7 +799,7 @@ struct RescSrc {
 template <bool WT, class MakeSrc>
 __device__ __forceinline__ void project_items_resc(const DevProblem& P, const Items& I, bool force_euclid,
                                                    MakeSrc make, double* dst, double* warm, long dbase, bool kkt) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int tid = thread_here(), lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int gpw = 64 / I.lg;
   const double* sx = P.Sx;
   for (int it = I.w0 + wv * gpw + lane / I.lg; it < I.w1; it += NWAVE * gpw) {
@@ -741,18 +844,19 @@ __device__ __forceinline__ void project_items_resc(const DevProblem& P, const It
 
 // warm (nullable): previous roots of the root-finding projections, one per
 // item (wave items first, then lane items), read as starting points and
-// overwritten with the new roots.  WT: dst is read by other workgroups
-template <bool EXT = false, bool WT = false, class MakeSrc>
+// overwritten with the new roots.  WT: dst is read by other workgroups;
+// LOCAL: dst is in LDS
+template <bool EXT = false, bool WT = false, bool RESC = EXT, bool LOCAL = false, class MakeSrc>
 __device__ __forceinline__ void project_items(const DevProblem& P, const Items& I, bool force_euclid, MakeSrc make,
                               double* dst, double* warm, unsigned long long* ptw = nullptr, long dbase = 0,
                               bool kkt = false) {
-  if constexpr (EXT) {
+  if constexpr (RESC) {
     if (P.resc) {
       project_items_resc<WT>(P, I, force_euclid, make, dst, warm, dbase, kkt);
       return;
     }
   }
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int tid = thread_here(), lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int gpw = 64 / I.lg;                       // groups per wave
   for (int it = I.w0 + wv * gpw + lane / I.lg; it < I.w1; it += NWAVE * gpw) {
     const long st = wi_start(P, I, it);
@@ -798,14 +902,15 @@ __device__ __forceinline__ void project_items(const DevProblem& P, const Items& 
       put<WT>(&dst[st + 2 - dbase], o.c);
     }
   }
-  __syncthreads();
+  if constexpr (LOCAL) lds_sync();
+  else __syncthreads();
 }
 
 // wave-uniform iteration over the coordinates of this workgroup's cone items
 // (same item-to-group mapping as project_items)
 template <class F>
 __device__ __forceinline__ void for_item_coords(const DevProblem& P, const Items& I, F f) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int tid = thread_here(), lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int gpw = 64 / I.lg;
   const int gl = lane & (I.lg - 1);
   for (int base = I.w0 + wv * gpw; base < I.w1; base += NWAVE * gpw) {
@@ -849,7 +954,7 @@ struct Own {
 // bytes of scratch a lane against 380 to 600).
 template <bool CONES, class MV, bool EXT, class Team>
 __device__ __forceinline__ void run_solver(const Run& A, const DevProblem& P, const DevVec& V, Ctl* ctl,
-                           const Team& T, Lds& L, const Own& own, bool prof) {
+                           const Team& T, LdsGen& L, const Own& own, bool prof) {
   const Bulk<MV> M(P);
   // LDS copy of the owned columns of R (bulk precision); the FP64 reads of
   // an FP32 run (start, checks) stay in global memory
@@ -944,7 +1049,7 @@ __device__ __forceinline__ void run_solver(const Run& A, const DevProblem& P, co
       });
     }
     hw_finish(R64, V.x, nullptr);
-    REDUCE_OR_EXIT(reduce_sh(T, L, nullptr, 0, r, L.C.hx, true));
+    REDUCE_OR_EXIT(reduce_sh(T, L, 0, 0, r, L.C.hx, true));
     for_rows_range(r0, r1, own.lr, [&](long row, int sub, bool act) {
       double ax = spmv_row(P.A_ptr, P.A_col, P.A_val, V.x, row, sub, own.lr, act);
       if (act && sub == 0) { V.Ax[row] = ax; V.Aa[row] = ax; V.ay[row] = V.y[row]; }
@@ -1040,38 +1145,12 @@ __device__ __forceinline__ void run_solver(const Run& A, const DevProblem& P, co
         const double a = f * V.s[st], b = f * V.s[st + 1], c = f * V.s[st + 2];
         const double la = fmin(a, 0.0), lc = fmax(c, 0.0);
         acc[1] += (a - la) * (a - la) + (c - lc) * (c - lc);
-        const double term = la == 0.0 ? b : (lc == 0.0 ? -INFINITY : b + la * (log(-la / lc) - 1.0));
+        const double term = la == 0.0 ? b : (lc == 0.0 ? -INFINITY : b + la * (log_call(-la / lc) - 1.0));
         acc[NSL - 1] += term / (P.nu_b * P.nu_c);
       }
     }
-    const int sl[3] = {SL_XQX, SL_RD2, SL_BOXD};
+    const unsigned long long sl = slot_list(SL_XQX, SL_RD2, SL_BOXD);
     block_store(L, acc, sl, NSL);
-  };
-
-  // residuals, objectives and status from the reduced slots SL_RP2, SL_RD2,
-  // SL_XQX, SL_CX, SL_BY (thread 0)
-  auto kkt_status = [&](Ctl& C, bool bad) __attribute__((always_inline)) {
-    const double* sc = L.scal;
-    const double scale = P.nu_b * P.nu_c;
-    C.rel_p = sqrt(sc[SL_RP2]) / (1.0 + P.norm_b);
-    C.rel_d = sqrt(sc[SL_RD2]) / (1.0 + P.norm_c);
-    C.pobj = scale * (0.5 * sc[SL_XQX] + sc[SL_CX]);
-    if constexpr (EXT) {
-      C.dobj = scale * (sc[SL_BY] + sc[SL_BOXD] - 0.5 * sc[SL_XQX]);
-      // a fixed-middle EXP reduced cost with lambda_a < 0 = lambda_c has
-      // dual value -inf: no gap closure yet
-      C.rel_gap = C.dobj == -INFINITY ? 1.0 : fabs(C.pobj - C.dobj) / (1.0 + fabs(C.pobj) + fabs(C.dobj));
-    } else {
-      C.dobj = scale * (sc[SL_BY] - 0.5 * sc[SL_XQX]);
-      C.rel_gap = fabs(C.pobj - C.dobj) / (1.0 + fabs(C.pobj) + fabs(C.dobj));
-    }
-    if (bad || !isfinite(C.rel_p) || !isfinite(C.rel_d) || !isfinite(C.rel_gap)) {
-      C.status = PDHCG_NUMERICAL;
-    } else if (fmax(C.rel_p, fmax(C.rel_d, C.rel_gap)) <= S.tol) {
-      C.status = PDHCG_OPTIMAL;
-    } else if (A.deadline != 0ull && wall_clock64() > A.deadline) {
-      C.status = PDHCG_TIME_LIMIT;
-    }
   };
 
   while (L.C.ktot < A.stop_at && L.C.status == 0) {
@@ -1170,7 +1249,7 @@ __device__ __forceinline__ void run_solver(const Run& A, const DevProblem& P, co
           if constexpr (SOLO) hw_add(L, RB, r, i, un, act);
         });
       }
-      const int sl[3] = {SL_DELTA2, SL_SJS, SL_SPS};
+      const unsigned long long sl = slot_list(SL_DELTA2, SL_SJS, SL_SPS);
       block_store(L, acc, sl, fuse ? 3 : 1);
       hw_finish(RB, V.u, fuse ? V.up : nullptr);
     }
@@ -1178,7 +1257,7 @@ __device__ __forceinline__ void run_solver(const Run& A, const DevProblem& P, co
     // -------------------------------------------------------------- inner loop
     int jcount = 0;
     if (P.q_diag) {
-      REDUCE_OR_EXIT(reduce_sh(T, L, nullptr, 0, 0, nullptr, true));
+      REDUCE_OR_EXIT(reduce_sh(T, L, 0, 0, 0, nullptr, true));
     } else {
       // With P diagonal or absent (fuse) an inner step takes one grid
       // synchronisation: the prox gradient g(u) = P u + R^T D R u + c +
@@ -1190,7 +1269,7 @@ __device__ __forceinline__ void run_solver(const Run& A, const DevProblem& P, co
       // before the step (two synchronisations).
       // (nothing but the sums crosses workgroups until the loop ends: the
       // one-sync step acquires once, after it; the other form gathers u)
-      const int sl_d[1] = {SL_DELTA2};
+      const unsigned long long sl_d = slot_list(SL_DELTA2);
       if (fuse) REDUCE_OR_EXIT(reduce_step(T, L, r, tau));
       else REDUCE_OR_EXIT(reduce_sh(T, L, sl_d, 1, r, L.hu, true));
       jcount = 1;
@@ -1224,7 +1303,7 @@ __device__ __forceinline__ void run_solver(const Run& A, const DevProblem& P, co
             V.g[i] = gc;
           });
           {
-            const int sl[3] = {SL_SJS, SL_SDG, SL_SS};
+            const unsigned long long sl = slot_list(SL_SJS, SL_SDG, SL_SS);
             block_store(L, acc, sl, 3);
             REDUCE_OR_EXIT(reduce_sh(T, L, sl, 3, 0, nullptr, false));
           }
@@ -1292,7 +1371,7 @@ __device__ __forceinline__ void run_solver(const Run& A, const DevProblem& P, co
           });
         }
         {
-          const int sl[3] = {SL_DELTA2, SL_SJS, SL_SPS};
+          const unsigned long long sl = slot_list(SL_DELTA2, SL_SJS, SL_SPS);
           block_store(L, acc, sl, fuse ? 3 : 1);
           hw_finish(RB, V.u, fuse ? V.up : nullptr);
         }
@@ -1353,7 +1432,7 @@ __device__ __forceinline__ void run_solver(const Run& A, const DevProblem& P, co
           put<WT>(&V.x[i], wi);
         }
       });
-      const int sl[4] = {SL_XMOV2, SL_RP2, SL_BY, SL_CX};
+      const unsigned long long sl = slot_list(SL_XMOV2, SL_RP2, SL_BY, SL_CX);
       block_store(L, acc, sl, ep_end ? 4 : 1);
       REDUCE_OR_EXIT(reduce_sh(T, L, sl, ep_end ? 4 : 1, 0, nullptr, true));
       if (tid == 0) {
@@ -1446,11 +1525,11 @@ __device__ __forceinline__ void run_solver(const Run& A, const DevProblem& P, co
         }
       });
       if (check) {
-        const int sl[8] = {SL_DY2, SL_ADXDY, SL_RP2, SL_BY, SL_MOVY2, SL_DX2, SL_MOVX2, SL_CX};
+        const unsigned long long sl = slot_list(SL_DY2, SL_ADXDY, SL_RP2, SL_BY, SL_MOVY2, SL_DX2, SL_MOVX2, SL_CX);
         block_store(L, acc, sl, 8);
         REDUCE_OR_EXIT(reduce_sh(T, L, sl, 8, 0, nullptr, true));
       } else {
-        const int sl[1] = {SL_XMOV2};
+        const unsigned long long sl = slot_list(SL_XMOV2);
         block_store(L, &acc[5], sl, 1);
         hw_finish(RB, V.x, nullptr);
         REDUCE_OR_EXIT(reduce_sh(T, L, sl, 1, r, L.C.hx, true));
@@ -1482,12 +1561,12 @@ __device__ __forceinline__ void run_solver(const Run& A, const DevProblem& P, co
     tmark(L, prof, PT_CHECK);
     dual_check(avg ? V.x : W, avg ? V.y : V.wy, avg ? L.C.hx : L.hu);
     {
-      const int sl[3] = {SL_XQX, SL_RD2, SL_BOXD};
+      const unsigned long long sl = slot_list(SL_XQX, SL_RD2, SL_BOXD);
       REDUCE_OR_EXIT(reduce_sh(T, L, sl, EXT ? 3 : 2, 0, nullptr, false));
     }
     if (avg) {
       if (tid == 0) {
-        kkt_status(L.C, false);
+        kkt_status<EXT>(P, A, L, false);
         L.C.k = 0;
         L.C.restarts += 1;
         if (tracing && rank == 0) {
@@ -1501,28 +1580,8 @@ __device__ __forceinline__ void run_solver(const Run& A, const DevProblem& P, co
       continue;
     }
     if (tid == 0) {
-      Ctl& C = L.C;
-      const double* sc = L.scal;
-      const double E2 = omega * sc[SL_DX2] + sc[SL_DY2] / omega + 2.0 * P.eta * sc[SL_ADXDY];
-      const double E = sqrt(fmax(E2, 0.0));
-      bool rs = false;
-      if (k == 0) C.E0 = E;
-      else rs = (E <= S.beta_s * C.E0) || (E <= S.beta_n * C.E0 && E > C.Eprev) ||
-                ((double)(k + 1) >= S.beta_a * (double)kt1);
-      C.Eprev = E;
-      C.lastE = E;
-      kkt_status(C, !isfinite(E));
-      if (C.status == 0 && rs) {
-        const double dxm = sqrt(sc[SL_MOVX2]), dym = sqrt(sc[SL_MOVY2]);
-        if (dxm > 1e-12 && dym > 1e-12) {
-          const double e = log(dym / (omega * dxm));
-          C.pid_I = S.pid_beta_i * C.pid_I + e;
-          C.omega = exp(log(omega) + S.pid_kp * e + S.pid_ki * C.pid_I + S.pid_kd * (e - C.e_prev));
-          C.e_prev = e;
-        }
-        C.k = 0;
-        C.restarts += 1;
-      }
+      double E;
+      const bool rs = check_step<EXT>(P, A, L, k, kt1, omega, E);
       L.done = rs ? 1 : 0;
       if (tracing && rank == 0) {
         double* t = TB.sc + (kt1 - 1) * 8;
@@ -1568,17 +1627,17 @@ __device__ __forceinline__ void run_solver(const Run& A, const DevProblem& P, co
         }
       });
       if (!restart) {
-        const int sl[1] = {SL_XMOV2};
+        const unsigned long long sl = slot_list(SL_XMOV2);
         block_store(L, &xm, sl, 1);
         hw_finish(RB, V.x, nullptr);
       }
     }
     if (restart) {
-      REDUCE_OR_EXIT(reduce_sh(T, L, nullptr, 0, 0, nullptr, true));
+      REDUCE_OR_EXIT(reduce_sh(T, L, 0, 0, 0, nullptr, true));
       if ((int)tid < r) L.C.hx[tid] = L.hu[tid];
       __syncthreads();
     } else {
-      const int sl[1] = {SL_XMOV2};
+      const unsigned long long sl = slot_list(SL_XMOV2);
       REDUCE_OR_EXIT(reduce_sh(T, L, sl, 1, r, L.C.hx, true));
       if (tid == 0) {
         L.C.eps_in = fmin(L.C.eps_in, fmax(S.gamma_in * sqrt(L.scal[SL_XMOV2]) / tau, S.eps_min));
@@ -1591,12 +1650,18 @@ __device__ __forceinline__ void run_solver(const Run& A, const DevProblem& P, co
 #undef PROJ
 }
 
+}  // namespace pdhcg
+
+#include "resident.hpp"
+
+namespace pdhcg {
+
 // ---------------------------------------------------------------------------
 // single-problem kernel: the whole grid is one team
 // ---------------------------------------------------------------------------
-template <class MV, bool SOLO, bool EXT, bool CONES = true>
-__device__ __forceinline__ void solve_body(const KArgs& A) {
-  __shared__ Lds L;
+// core: run(Run, L, Own) on an L of its own type
+template <class LdsT, class Core>
+__device__ __forceinline__ void solve_body(const KArgs& A, LdsT& L, Core core) {
   const int rank = blockIdx.x;
   if (threadIdx.x < PT_COUNT) L.pt[threadIdx.x] = 0ull;
   if (threadIdx.x == 0) {
@@ -1622,12 +1687,7 @@ __device__ __forceinline__ void solve_body(const KArgs& A) {
   own.atseg = P.at_perm ? P.at_seg + (kClasses + 1) * rank : nullptr;
   extern __shared__ __align__(16) unsigned char dyn_lds[];
   const Run run{&A.S, &A.T, A.stop_at, A.qmax, 0ull, A.lds_bytes > 0 ? dyn_lds : nullptr, A.lds_bytes};
-  if constexpr (SOLO) {
-    run_solver<CONES, MV, EXT>(run, P, A.V, A.ctl, SoloTeam{}, L, own, prof);
-  } else {
-    GridTeam T{A.comm, A.spin_limit, rank, (int)gridDim.x};
-    run_solver<CONES, MV, EXT>(run, P, A.V, A.ctl, T, L, own, prof);
-  }
+  core(run, own, prof, reinterpret_cast<double*>(dyn_lds));
   tmark(L, prof, PT_INIT);
   __syncthreads();
   if (prof && threadIdx.x < PT_COUNT) A.ptimes[(size_t)rank * PT_COUNT + threadIdx.x] += L.pt[threadIdx.x];
@@ -1637,31 +1697,75 @@ __device__ __forceinline__ void solve_body(const KArgs& A) {
   }
 }
 
-__global__ __launch_bounds__(BLOCK) void solve_kernel(KArgs A) { solve_body<double, false, false>(A); }
+template <class MV, bool SOLO, bool EXT, bool CONES = true>
+__device__ __forceinline__ void solve_general(const KArgs& A) {
+  __shared__ LdsGen L;
+  solve_body(A, L, [&](const Run& run, const Own& own, bool prof, double*) __attribute__((always_inline)) {
+    if constexpr (SOLO) {
+      run_solver<CONES, MV, EXT>(run, A.P, A.V, A.ctl, SoloTeam{}, L, own, prof);
+    } else {
+      const GridTeam T{A.comm, A.spin_limit, (int)blockIdx.x, (int)gridDim.x};
+      run_solver<CONES, MV, EXT>(run, A.P, A.V, A.ctl, T, L, own, prof);
+    }
+  });
+}
+
+template <int CPT, int RPT, bool SOLO, bool CONES, int Q>
+__device__ __forceinline__ void solve_resident() {
+  __shared__ LdsRes L;
+  // the kernel's argument, in the kernarg segment
+  const KArgs& A = *(const KArgs*)(const __attribute__((address_space(4))) KArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+  solve_body(A, L, [&](const Run& run, const Own& own, bool prof, double* dyn) __attribute__((always_inline)) {
+    if constexpr (SOLO) {
+      run_resident<CPT, RPT, CONES, Q>(run, A.P, A.V, A.ctl, SoloTeam{}, L, own, prof, dyn);
+    } else {
+      const GridTeam T{A.comm, A.spin_limit, (int)blockIdx.x, (int)gridDim.x};
+      run_resident<CPT, RPT, CONES, Q>(run, A.P, A.V, A.ctl, T, L, own, prof, dyn);
+    }
+  });
+}
+
+// problems that the register-resident core takes (P.res): one or two
+// coordinates and rows a thread, with cone blocks or without, diagonal or
+// general Q; and one workgroup
+#define RESIDENT(name, cpt, cones, q) \
+  __global__ __launch_bounds__(BLOCK) void name(KArgs) { solve_resident<cpt, cpt, false, cones, q>(); }
+RESIDENT(resident_kernel1_diag, 1, true, Q_DIAG)
+RESIDENT(resident_kernel1, 1, true, Q_GENERAL)
+RESIDENT(resident_kernel1_lin_diag, 1, false, Q_DIAG)
+RESIDENT(resident_kernel1_lin, 1, false, Q_GENERAL)
+RESIDENT(resident_kernel2_diag, 2, true, Q_DIAG)
+RESIDENT(resident_kernel2, 2, true, Q_GENERAL)
+RESIDENT(resident_kernel2_lin_diag, 2, false, Q_DIAG)
+RESIDENT(resident_kernel2_lin, 2, false, Q_GENERAL)
+#undef RESIDENT
+__global__ __launch_bounds__(BLOCK) void resident_kernel_one(KArgs) { solve_resident<1, 1, true, true, Q_ANY>(); }
+
+__global__ __launch_bounds__(BLOCK) void solve_kernel(KArgs A) { solve_general<double, false, false>(A); }
 
 // row bounds, boxes and fixed-middle EXP blocks
-__global__ __launch_bounds__(BLOCK) void solve_kernel_ext(KArgs A) { solve_body<double, false, true>(A); }
+__global__ __launch_bounds__(BLOCK) void solve_kernel_ext(KArgs A) { solve_general<double, false, true>(A); }
 
 // problems without cone blocks (FREE / R+ only, no EXT feature): compiled
 // without the projection code, at 4 waves per SIMD (two workgroups per CU),
 // so twice the gathers of the latency-bound products are in flight
-__global__ __launch_bounds__(BLOCK, 4) void solve_kernel_lin(KArgs A) { solve_body<double, false, false, false>(A); }
+__global__ __launch_bounds__(BLOCK, 4) void solve_kernel_lin(KArgs A) { solve_general<double, false, false, false>(A); }
 // the same with row bounds and boxes (no fixed-middle EXP blocks: those are
 // cone items)
-__global__ __launch_bounds__(BLOCK, 4) void solve_kernel_lin_ext(KArgs A) { solve_body<double, false, true, false>(A); }
+__global__ __launch_bounds__(BLOCK, 4) void solve_kernel_lin_ext(KArgs A) { solve_general<double, false, true, false>(A); }
 
 // FP32 bulk sweeps (FP32 copies of A, A^T, P, R); everything else as above
-__global__ __launch_bounds__(BLOCK) void solve_kernel_f32(KArgs A) { solve_body<float, false, false>(A); }
-__global__ __launch_bounds__(BLOCK) void solve_kernel_f32_ext(KArgs A) { solve_body<float, false, true>(A); }
+__global__ __launch_bounds__(BLOCK) void solve_kernel_f32(KArgs A) { solve_general<float, false, false>(A); }
+__global__ __launch_bounds__(BLOCK) void solve_kernel_f32_ext(KArgs A) { solve_general<float, false, true>(A); }
 // and without cone blocks, at two workgroups per CU like the FP64 cone-free
 // kernels (the FP64 polish runs those on the same grid)
-__global__ __launch_bounds__(BLOCK, 4) void solve_kernel_f32_lin(KArgs A) { solve_body<float, false, false, false>(A); }
-__global__ __launch_bounds__(BLOCK, 4) void solve_kernel_f32_lin_ext(KArgs A) { solve_body<float, false, true, false>(A); }
+__global__ __launch_bounds__(BLOCK, 4) void solve_kernel_f32_lin(KArgs A) { solve_general<float, false, false, false>(A); }
+__global__ __launch_bounds__(BLOCK, 4) void solve_kernel_f32_lin_ext(KArgs A) { solve_general<float, false, true, false>(A); }
 
 // a grid of one workgroup: workgroup barriers and the single-workgroup
 // reductions of the batch kernels (the same arithmetic as a batch solve)
-__global__ __launch_bounds__(BLOCK) void solve_kernel_one(KArgs A) { solve_body<double, true, false>(A); }
-__global__ __launch_bounds__(BLOCK) void solve_kernel_one_ext(KArgs A) { solve_body<double, true, true>(A); }
+__global__ __launch_bounds__(BLOCK) void solve_kernel_one(KArgs A) { solve_general<double, true, false>(A); }
+__global__ __launch_bounds__(BLOCK) void solve_kernel_one_ext(KArgs A) { solve_general<double, true, true>(A); }
 
 // ---------------------------------------------------------------------------
 // setup kernels: CSR SpMV and deterministic two-pass norms (power iteration)
@@ -1824,10 +1928,10 @@ __global__ __launch_bounds__(BLOCK) void dual_slack_kernel(DevProblem P, const d
 // batch kernels: independent instances, one workgroup per instance at a time
 // ---------------------------------------------------------------------------
 // before every batch launch: control blocks zeroed, scaled warm starts (or
-// zeros) into zb and y, root warm starts unset (NaN), queue at 0
+// zeros) into zb and y, root warm starts unset (NaN), both queues at 0
 __global__ __launch_bounds__(BLOCK) void batch_reset_kernel(const InstDesc* desc, int count,
                                                            int* queue) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) queue[0] = 0;
+  if (blockIdx.x == 0 && threadIdx.x < 2) queue[threadIdx.x] = 0;
   for (int i = blockIdx.x; i < count; i += gridDim.x) {
     const InstDesc& D = desc[i];
     const long n = D.P.n, m = D.P.m;
@@ -1842,15 +1946,14 @@ __global__ __launch_bounds__(BLOCK) void batch_reset_kernel(const InstDesc* desc
 // persistent batch solve: each workgroup takes the next queue position,
 // solves that instance to termination with the single-workgroup team, and
 // stores its control block; instances are queued largest first
-template <bool CONES, bool EXT>
-__device__ __forceinline__ void batch_body(const BatchArgs& B) {
-  __shared__ Lds L;
+template <class LdsT, class Core>
+__device__ __forceinline__ void batch_body(const BatchArgs& B, LdsT& L, Core core) {
   __shared__ int slot;
   const unsigned long long deadline = B.limit_ticks ? wall_clock64() + B.limit_ticks : 0ull;
   const bool prof = B.ptimes != nullptr;
   if (threadIdx.x < PT_COUNT) L.pt[threadIdx.x] = 0ull;
   for (;;) {
-    if (threadIdx.x == 0) slot = atomicAdd(B.queue, 1);
+    if (threadIdx.x == 0) slot = B.first + atomicAdd(B.queue, 1);
     __syncthreads();
     const int q = __builtin_amdgcn_readfirstlane(slot);
     if (q >= B.count) break;
@@ -1875,22 +1978,44 @@ __device__ __forceinline__ void batch_body(const BatchArgs& B) {
       own.atperm = nullptr;
       own.atseg = nullptr;
       const Run run{&B.S, &D.T, B.stop_at, D.qmax, deadline, nullptr, 0};
-      run_solver<CONES, double, EXT>(run, D.P, D.V, D.ctl, SoloTeam{}, L, own, prof);
+      core(run, D, own, prof);
       tmark(L, prof, PT_INIT);
       __syncthreads();
       if (threadIdx.x == 0) *D.ctl = L.C;
     }
     __syncthreads();
   }
-  if (prof && threadIdx.x < PT_COUNT) B.ptimes[(size_t)blockIdx.x * PT_COUNT + threadIdx.x] = L.pt[threadIdx.x];
+  if (prof && threadIdx.x < PT_COUNT) B.ptimes[(size_t)blockIdx.x * PT_COUNT + threadIdx.x] += L.pt[threadIdx.x];
 }
 
-__global__ __launch_bounds__(BLOCK) void batch_kernel(BatchArgs B) { batch_body<true, false>(B); }
-__global__ __launch_bounds__(BLOCK) void batch_kernel_ext(BatchArgs B) { batch_body<true, true>(B); }
+template <bool CONES, bool EXT>
+__device__ __forceinline__ void batch_general(const BatchArgs& B) {
+  __shared__ LdsGen L;
+  batch_body(B, L, [&](const Run& run, const InstDesc& D, const Own& own, bool prof) __attribute__((always_inline)) {
+    run_solver<CONES, double, EXT>(run, D.P, D.V, D.ctl, SoloTeam{}, L, own, prof);
+  });
+}
+
+template <bool CONES>
+__device__ __forceinline__ void batch_resident(const BatchArgs& B) {
+  __shared__ LdsRes L;
+  extern __shared__ __align__(16) unsigned char dyn_lds[];
+  batch_body(B, L, [&](const Run& run, const InstDesc& D, const Own& own, bool prof) __attribute__((always_inline)) {
+    double* dyn = reinterpret_cast<double*>(dyn_lds);
+    run_resident<1, 1, CONES, Q_ANY>(run, D.P, D.V, D.ctl, SoloTeam{}, L, own, prof, dyn);
+  });
+}
+
+__global__ __launch_bounds__(BLOCK) void batch_kernel(BatchArgs B) { batch_general<true, false>(B); }
+__global__ __launch_bounds__(BLOCK) void batch_kernel_ext(BatchArgs B) { batch_general<true, true>(B); }
 
 // batches without cone blocks: 4 waves per SIMD (two instances per CU)
-__global__ __launch_bounds__(BLOCK, 4) void batch_kernel_lin(BatchArgs B) { batch_body<false, false>(B); }
-__global__ __launch_bounds__(BLOCK, 4) void batch_kernel_lin_ext(BatchArgs B) { batch_body<false, true>(B); }
+__global__ __launch_bounds__(BLOCK, 4) void batch_kernel_lin(BatchArgs B) { batch_general<false, false>(B); }
+__global__ __launch_bounds__(BLOCK, 4) void batch_kernel_lin_ext(BatchArgs B) { batch_general<false, true>(B); }
+
+// the instances of a batch that the register-resident core takes
+__global__ __launch_bounds__(BLOCK) void batch_kernel_res(BatchArgs B) { batch_resident<true>(B); }
+__global__ __launch_bounds__(BLOCK) void batch_kernel_res_lin(BatchArgs B) { batch_resident<false>(B); }
 
 // ||A^||_2 of every instance: the power iteration of the single-problem
 // setup (128 steps of A^T A from 1/sqrt(n), normalised each step), one
@@ -2027,7 +2152,16 @@ int block_size() { return BLOCK; }
 // hang).
 // the solver kernel of a launch: FP32 bulk or FP64, a grid of one
 // workgroup, the EXT features, problems without cone blocks
-static const void* solver_kernel_for(bool fp32, bool ext, bool cones, int grid) {
+static const void* solver_kernel_for(int res, bool qdiag, bool fp32, bool ext, bool cones, int grid) {
+  if (res == RES_GRID1 || res == RES_GRID2) {
+    static const void* const k[2][2][2] = {
+        {{(const void*)resident_kernel1_lin, (const void*)resident_kernel1_lin_diag},
+         {(const void*)resident_kernel1, (const void*)resident_kernel1_diag}},
+        {{(const void*)resident_kernel2_lin, (const void*)resident_kernel2_lin_diag},
+         {(const void*)resident_kernel2, (const void*)resident_kernel2_diag}}};
+    return k[res == RES_GRID2][cones][qdiag];
+  }
+  if (res == RES_ONE) return (const void*)resident_kernel_one;
   if (fp32) {
     if (ext) return cones ? (const void*)solve_kernel_f32_ext : (const void*)solve_kernel_f32_lin_ext;
     return cones ? (const void*)solve_kernel_f32 : (const void*)solve_kernel_f32_lin;
@@ -2037,14 +2171,20 @@ static const void* solver_kernel_for(bool fp32, bool ext, bool cones, int grid) 
   return cones ? (const void*)solve_kernel : (const void*)solve_kernel_lin;
 }
 
+// dynamic LDS beyond 64 KiB has to be asked for
+static hipError_t allow_lds(const void* k, int bytes) {
+  return bytes > 0 ? hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) : hipSuccess;
+}
+
 hipError_t launch_solve(const KArgs& args, bool fp32, int grid, hipStream_t stream) {
   KArgs a = args;
   void* params[] = {&a};
   const bool ext = args.P.ext != 0;
   const bool cones = args.P.n_wave > 0 || args.P.n_lane > 0;
-  const void* k = solver_kernel_for(fp32, ext, cones, grid);
+  const void* k = solver_kernel_for(args.P.res, args.P.q_diag != 0, fp32, ext, cones, grid);
   int dev = 0, ncu = 0, per = 0;
-  hipError_t e = hipGetDevice(&dev);
+  hipError_t e = allow_lds(k, args.lds_bytes);
+  if (e == hipSuccess) e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
   if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k, BLOCK, (size_t)args.lds_bytes);
   if (e != hipSuccess) return e;
@@ -2059,18 +2199,30 @@ hipError_t max_resident_grid_for(bool fp32, bool ext, bool cones, int lds_bytes,
   if (e != hipSuccess) return e;
   // FP32 mode polishes in FP64 on the same grid: both kernels must fit
   int per = 0, per64 = 0;
-  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per64, solver_kernel_for(false, ext, cones, 2), BLOCK,
+  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per64, solver_kernel_for(RES_NONE, false, false, ext, cones, 2), BLOCK,
                                                    (size_t)lds_bytes);
   if (e != hipSuccess) return e;
   per = per64;
   if (fp32) {
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, solver_kernel_for(true, ext, cones, 2), BLOCK,
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, solver_kernel_for(RES_NONE, false, true, ext, cones, 2), BLOCK,
                                                      (size_t)lds_bytes);
     if (e != hipSuccess) return e;
     per = std::min(per, per64);
   }
   *out = per * ncu;
   return hipSuccess;
+}
+
+// workgroups of the register-resident grid kernel resident at once
+hipError_t max_resident_grid_res(bool cones, int lds_bytes, int* out) {
+  int dev = 0, ncu = 0, per = 0;
+  const void* k = solver_kernel_for(RES_GRID2, false, false, false, cones, 2);
+  hipError_t e = allow_lds(k, lds_bytes);
+  if (e == hipSuccess) e = hipGetDevice(&dev);
+  if (e == hipSuccess) e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
+  if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k, BLOCK, (size_t)lds_bytes);
+  *out = e == hipSuccess ? per * ncu : 0;
+  return e;
 }
 
 hipError_t launch_spmv(const int64_t* ptr, const int* col, const double* val, const double* x,
@@ -2193,24 +2345,29 @@ hipError_t launch_project(int type, int dim, long count, const double* alpha, co
   return hipGetLastError();
 }
 
-static const void* batch_kernel_for(bool cones, bool ext) {
+static const void* batch_kernel_for(bool res, bool cones, bool ext) {
+  if (res) return cones ? (const void*)batch_kernel_res : (const void*)batch_kernel_res_lin;
   return cones ? (ext ? (const void*)batch_kernel_ext : (const void*)batch_kernel)
                : (ext ? (const void*)batch_kernel_lin_ext : (const void*)batch_kernel_lin);
 }
 
-int batch_grid_limit(bool cones, bool ext) {
+int batch_grid_limit(bool res, bool cones, bool ext, int lds_bytes) {
   int dev = 0, ncu = 0, per = 0;
   if (hipGetDevice(&dev) != hipSuccess) return 256;
   if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 256;
-  const void* k = batch_kernel_for(cones, ext);
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k, BLOCK, 0) != hipSuccess) return ncu;
+  const void* k = batch_kernel_for(res, cones, ext);
+  if (allow_lds(k, lds_bytes) != hipSuccess) return ncu;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k, BLOCK, (size_t)lds_bytes) != hipSuccess) return ncu;
   return std::max(1, per * ncu);
 }
 
-hipError_t launch_batch(const BatchArgs& args, bool cones, bool ext, int grid, hipStream_t st) {
+hipError_t launch_batch(const BatchArgs& args, bool res, bool cones, bool ext, int lds_bytes, int grid,
+                        hipStream_t st) {
   BatchArgs a = args;
   void* params[] = {&a};
-  return hipLaunchKernel(batch_kernel_for(cones, ext), dim3(grid), dim3(BLOCK), params, 0, st);
+  const void* k = batch_kernel_for(res, cones, ext);
+  hipError_t e = allow_lds(k, lds_bytes);
+  return e != hipSuccess ? e : hipLaunchKernel(k, dim3(grid), dim3(BLOCK), params, (size_t)lds_bytes, st);
 }
 
 hipError_t launch_batch_reset(const InstDesc* desc, int count, int* queue, hipStream_t st) {
@@ -2220,7 +2377,7 @@ hipError_t launch_batch_reset(const InstDesc* desc, int count, int* queue, hipSt
 }
 
 hipError_t launch_batch_power(const InstDesc* desc, int count, int iters, double* out, hipStream_t st) {
-  const int grid = std::max(1, std::min(count, batch_grid_limit(false, false)));
+  const int grid = std::max(1, std::min(count, batch_grid_limit(false, false, false, 0)));
   hipLaunchKernelGGL(batch_power_kernel, dim3(grid), dim3(BLOCK), 0, st, desc, count, iters, out);
   return hipGetLastError();
 }

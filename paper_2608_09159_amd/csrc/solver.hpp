@@ -10,6 +10,7 @@ int block_size();
 hipError_t launch_solve(const KArgs& args, bool fp32, int grid, hipStream_t stream);
 // workgroups resident at once for the kernel(s) a solve of this kind runs
 hipError_t max_resident_grid_for(bool fp32, bool ext, bool cones, int lds_bytes, int* out);
+hipError_t max_resident_grid_res(bool cones, int lds_bytes, int* out);
 hipError_t launch_spmv(const int64_t* ptr, const int* col, const double* val, const double* x,
                        double* y, long rows, int Lw, hipStream_t st);
 // rows of perm in five length classes (seg[0..5]: class boundaries in perm)
@@ -40,9 +41,11 @@ hipError_t read_cone_failure(double rec[8], unsigned* count);
 hipError_t launch_project(int type, int dim, long count, const double* alpha, const double* r,
                           const double* m, double* out, hipStream_t st);
 
-// batch solve (one workgroup per instance)
-int batch_grid_limit(bool cones, bool ext);
-hipError_t launch_batch(const BatchArgs& args, bool cones, bool ext, int grid, hipStream_t st);
+// batch solve (one workgroup per instance); res: the instances of the
+// register-resident core
+int batch_grid_limit(bool res, bool cones, bool ext, int lds_bytes);
+hipError_t launch_batch(const BatchArgs& args, bool res, bool cones, bool ext, int lds_bytes, int grid,
+                        hipStream_t st);
 hipError_t launch_batch_reset(const InstDesc* desc, int count, int* queue, hipStream_t st);
 hipError_t launch_batch_power(const InstDesc* desc, int count, int iters, double* out, hipStream_t st);
 hipError_t launch_batch_gather(const InstDesc* desc, int count, const long* offx, const long* offy,
