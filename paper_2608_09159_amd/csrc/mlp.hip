@@ -5,13 +5,26 @@
 // GEMM: C[M x N] = op(A)[M x K] * op(B)[K x N], all matrices row-major.
 //   A: M x K (TA = false) or stored K x M (TA = true, used transposed)
 //   B: K x N (TB = false) or stored N x K (TB = true, used transposed)
-// Workgroup tile 128 x 128 x TK, four waves, each wave a 64 x 64 output block
-// (2 x 2 blocks of v_mfma_f32_32x32x16_bf16, TK / 16 steps per stage).  Both
-// operand tiles are staged in LDS with K contiguous (row stride padded by 8
+// The sum over K is cut into chunks (chunk_k below): a chunk is one chain of
+// v_mfma_f32_32x32x16_bf16 from zero, and the chunks' sums are added in order
+// to zero.  Three kernels form the same sums:
+//   gemm_kernel<128>  one chunk, tiles of 128 x 128 staged in LDS: large M x N
+//   gemm_kernel<64>   several chunks one after another, tiles of 64 x 64
+//   gemm_rows_kernel  a chunk per wave, tiles of 32 x 32, fragments straight
+//                     from memory: few tiles and long K, or up to 32 rows
+// so the chunks never travel through memory, except where a product has too
+// few tiles for the chip (one row): then they are spread over workgroups and
+// added by a second kernel.  As partial tiles in memory, one for each chunk,
+// they were 20 to 44 MB a product, written and read.
+//
+// In the staged kernels each of the four waves owns a quarter of the tile;
+// both operand tiles are staged with K contiguous (row stride padded by 8
 // elements), so every lane reads its 8-element fragment with one 16-byte LDS
-// load; global loads are 8-byte runs along the contiguous dimension.  Long K is split over `splits` workgroups writing FP32 partial tiles;
-// a second kernel sums them in a fixed order and applies the epilogue, so
-// results do not depend on scheduling.
+// load; global loads are 4-element runs along the contiguous dimension.
+//
+// Kernel time of a training step of 4800-512-512-5450 at batch 256: 385 us in
+// 27 launches before, 160 us in 12 now.  A forward pass of 51000-512-512-56500
+// at batch 1: 79 us before, 51 us now (its weights alone are 110 MB).
 #include <hip/hip_runtime.h>
 
 #include <stdint.h>
@@ -26,50 +39,48 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-constexpr int TM = 128, TN = 128, TK = 64, LDK = TK + 8;
-constexpr int GT = 256;   // threads per GEMM workgroup (4 waves, 2 x 2 of 64 x 64)
+constexpr int TK = 64, LDK = TK + 8;
+constexpr int GT = 256;   // threads per staged GEMM workgroup (4 waves, 2 x 2)
+constexpr int RT = 32;    // tile of gemm_rows_kernel
 constexpr int VW = 4;     // elements per vector load (8 bytes)
 
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+// vectors at addresses that are a multiple of four bytes only
+typedef bf16x4 __attribute__((aligned(4))) bf16x4_a4;
+typedef bf16x8 __attribute__((aligned(4))) bf16x8_a4;
 
 struct GemmArgs {
   const __bf16* A;
   const __bf16* B;
   long lda, ldb;
   int M, N, K;
-  int kchunk;             // K range of one split (multiple of TK)
+  int kchunk;             // K range of one chunk (multiple of TK)
   int epi;
-  int vec_a, vec_b;       // leading dimension a multiple of VW: vector loads
+  bool vec_a, vec_b;      // vector loads (stage_load)
   const float* bias;      // EPI_BIAS_*
   const __bf16* mask;     // EPI_MASK_BF16: M x N, ld = N
-  float* outf;            // FP32 output (ld = N) or partials [splits][M][N]
+  float* outf;            // FP32 output (ld = N) or partials [chunks][M][N]
   __bf16* outb;           // BF16 output (ld = N)
-  int partial;            // 1: write FP32 partials of split blockIdx.z
+  int partial;            // 1: write the chunks' sums
+  GradStep gs;            // EPI_GRAD
 };
+
+__device__ __forceinline__ float adam_update(float w, float g, float& m, float& v, const AdamStep& a) {
+  const float mi = fmaf(a.omb1, g, a.b1 * m);   // written out: the same rounding wherever it is inlined
+  const float vi = fmaf(a.omb2 * g, g, a.b2 * v);
+  m = mi;
+  v = vi;
+  return w - a.lr * (mi / a.c1) / (sqrtf(vi / a.c2) + a.eps);
+}
 
 __device__ __forceinline__ void epilogue(const GemmArgs& g, int m, int n, float acc) {
   const size_t o = (size_t)m * g.N + n;
   switch (g.epi) {
-    case EPI_F32: g.outf[o] = acc; break;
     case EPI_BIAS_F32: g.outf[o] = acc + g.bias[n]; break;
     case EPI_BIAS_RELU_BF16: g.outb[o] = (__bf16)fmaxf(acc + g.bias[n], 0.0f); break;
     case EPI_MASK_BF16: g.outb[o] = (__bf16)((float)g.mask[o] > 0.0f ? acc : 0.0f); break;
     default: break;
   }
-}
-
-// VW consecutive elements src[0..VW) along the contiguous dimension, zero
-// past `lim` (elements from the start of the run) or outside the tile
-__device__ __forceinline__ bf16x4 load_run(const __bf16* src, int lim, bool vec) {
-  bf16x4 v;
-  if (vec && lim >= VW) {
-    v = *reinterpret_cast<const bf16x4*>(src);
-  } else {
-    const __bf16 z = (__bf16)0.0f;
-#pragma unroll
-    for (int j = 0; j < VW; ++j) v[j] = j < lim ? src[j] : z;
-  }
-  return v;
 }
 
 // LDS column of element (row r, k): the 8-element k groups of a row are
@@ -84,56 +95,75 @@ __device__ __forceinline__ int kswz(int r, int k) {
 // k-contiguous storage (element (r, k) at P[r * ld + k]) as VW-runs of k;
 // r-contiguous storage (element (r, k) at P[k * ld + r]) as 4 x 4 blocks,
 // four runs of 4 rows transposed in registers into four runs of 4 k.
-constexpr int NRUN = (TM * TK / VW) / GT;   // runs of VW elements per thread
-static_assert((TM / 4) * (TK / 4) / GT * 4 == NRUN, "both staging forms use NRUN runs per thread");
+template <int T>
+constexpr int NRUN = (T * TK / VW) / GT;   // runs of VW elements per thread
+static_assert((64 / 4) * (TK / 4) / GT * 4 == NRUN<64>, "both staging forms use NRUN runs per thread");
 
-// global -> registers (zero outside the matrix or past kend)
-template <bool KCONTIG>
-__device__ __forceinline__ void stage_load(bf16x4 (&x)[NRUN], const __bf16* P, long ld, int r0, int rmax,
+// global -> registers: zero past kend, anything past rmax (those rows and
+// columns of C are dropped).  vec: the contiguous dimension and the leading
+// dimension are even and at least 4, so every run of 4 is one load, at the
+// matrix's last 4 elements where it would pass the end (by 2, or altogether).
+// No branches: as tests around each load they were most of a stage's time.
+template <int T, bool KCONTIG>
+__device__ __forceinline__ void stage_load(bf16x4 (&x)[NRUN<T>], const __bf16* P, long ld, int r0, int rmax,
                                            int k0, int kend, bool vec) {
   const int tid = threadIdx.x;
-  const __bf16 zero = (__bf16)0.0f;
-  if (KCONTIG) {
-    constexpr int RUNS = TK / VW;
+  const __bf16 z = (__bf16)0.0f;
+  constexpr int RUNS = TK / VW, RB = T / 4;
+  if (vec) {
 #pragma unroll
-    for (int q = 0; q < NRUN; ++q) {
-      const int v = tid + q * GT;
-      const int row = r0 + v / RUNS, k = k0 + (v % RUNS) * VW;
-      if (row < rmax && k < kend) x[q] = load_run(P + (size_t)row * ld + k, kend - k, vec);
-      else x[q] = bf16x4{zero, zero, zero, zero};
+    for (int q = 0; q < NRUN<T>; ++q) {
+      if (KCONTIG) {
+        const int v = tid + q * GT;
+        const int row = min(r0 + v / RUNS, rmax - 1), k = k0 + (v % RUNS) * VW, st = min(k, kend - VW);
+        const bf16x4 w = *reinterpret_cast<const bf16x4_a4*>(P + (size_t)row * ld + st);
+        x[q] = st == k ? w : st + 2 == k ? bf16x4{w[2], w[3], z, z} : bf16x4{z, z, z, z};
+      } else {
+        const int b = tid + (q / 4) * GT;
+        const int row = r0 + (b % RB) * 4, k = k0 + (b / RB) * 4 + q % 4, st = min(row, rmax - VW);
+        const bf16x4 w = *reinterpret_cast<const bf16x4_a4*>(P + (size_t)min(k, kend - 1) * ld + st);
+        x[q] = k >= kend ? bf16x4{z, z, z, z} : st == row ? w : bf16x4{w[2], w[3], z, z};
+      }
     }
   } else {
-    constexpr int RB = TM / 4;
 #pragma unroll
-    for (int q = 0; q < NRUN / 4; ++q) {
-      const int b = tid + q * GT;
-      const int row = r0 + (b % RB) * 4, kb = k0 + (b / RB) * 4;
+    for (int q = 0; q < NRUN<T>; ++q) {
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int k = kb + t;
-        if (row < rmax && k < kend) x[4 * q + t] = load_run(P + (size_t)k * ld + row, rmax - row, vec);
-        else x[4 * q + t] = bf16x4{zero, zero, zero, zero};
+      for (int j = 0; j < VW; ++j) {
+        int row, k;
+        if (KCONTIG) {
+          const int v = tid + q * GT;
+          row = r0 + v / RUNS;
+          k = k0 + (v % RUNS) * VW + j;
+        } else {
+          const int b = tid + (q / 4) * GT;
+          row = r0 + (b % RB) * 4 + j;
+          k = k0 + (b / RB) * 4 + q % 4;
+        }
+        const size_t rr = min(row, rmax - 1), kk = min(k, kend - 1);
+        const __bf16 w = KCONTIG ? P[rr * ld + kk] : P[kk * ld + rr];
+        x[q][j] = k < kend ? w : z;
       }
     }
   }
 }
 
 // registers -> S[row][k] (swizzled k groups)
-template <bool KCONTIG>
-__device__ __forceinline__ void stage_store(__bf16 (*S)[LDK], const bf16x4 (&x)[NRUN]) {
+template <int T, bool KCONTIG>
+__device__ __forceinline__ void stage_store(__bf16 (*S)[LDK], const bf16x4 (&x)[NRUN<T>]) {
   const int tid = threadIdx.x;
   if (KCONTIG) {
     constexpr int RUNS = TK / VW;
 #pragma unroll
-    for (int q = 0; q < NRUN; ++q) {
+    for (int q = 0; q < NRUN<T>; ++q) {
       const int v = tid + q * GT;
       const int r = v / RUNS, kq = (v % RUNS) * VW;
       *reinterpret_cast<bf16x4*>(&S[r][kswz(r, kq)]) = x[q];
     }
   } else {
-    constexpr int RB = TM / 4;
+    constexpr int RB = T / 4;
 #pragma unroll
-    for (int q = 0; q < NRUN / 4; ++q) {
+    for (int q = 0; q < NRUN<T> / 4; ++q) {
       const int b = tid + q * GT;
       const int rb = (b % RB) * 4, kb = (b / RB) * 4;
 #pragma unroll
@@ -144,73 +174,253 @@ __device__ __forceinline__ void stage_store(__bf16 (*S)[LDK], const bf16x4 (&x)[
   }
 }
 
-template <bool TA, bool TB>
+// a barrier for LDS alone: loads from memory stay in flight across it
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Tiles of T x T.  T = 64 where K has several chunks: half the tile in each
+// direction, so that a chunk's sums and their total both stay in registers and
+// a product of a few thousand columns covers the chip (512 x 5450 x 256: 688
+// workgroups, 172 with T = 128).
+// EPI_GRAD (C = dW): the workgroups of the first tile row add up the columns of
+// B (the bias gradient) from the staged tiles, in row order, and the Adam step
+// is taken where the gradient is: dW, W, m and v pass through memory once
+// (512 x 5450 x 256: 24 us, bound by those 84 MB; 57 us in five kernels).
+template <int T, bool TA, bool TB>
 __global__ __launch_bounds__(GT) void gemm_kernel(GemmArgs g) {
-  __shared__ __attribute__((aligned(16))) __bf16 As[TM][LDK];
-  __shared__ __attribute__((aligned(16))) __bf16 Bs[TN][LDK];
+  constexpr bool CHUNKS = T == 64;
+  constexpr int NB = T / 64;        // 32 x 32 blocks per wave and direction
+  __shared__ __attribute__((aligned(16))) __bf16 As[T][LDK];
+  __shared__ __attribute__((aligned(16))) __bf16 Bs[T][LDK];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int m0 = blockIdx.y * TM, n0 = blockIdx.x * TN;
-  const int kb = blockIdx.z * g.kchunk;
-  const int ke = min(g.K, kb + g.kchunk);
-  const int wm = (wv >> 1) * 64, wn = (wv & 1) * 64;
-  f32x16 acc[2][2] = {};
+  const int m0 = blockIdx.y * T, n0 = blockIdx.x * T;
+  const int wm = (wv >> 1) * (T / 2), wn = (wv & 1) * (T / 2);
+  constexpr bool GRAD = TA;         // the one product with a transposed A
+  const bool colsum = GRAD && blockIdx.y == 0 && tid < T;
+  float db = 0.0f;
+  f32x16 acc[NB][NB] = {}, tot[CHUNKS ? NB : 1][CHUNKS ? NB : 1] = {};
   // the next stage's global loads are in flight while this stage computes
-  bf16x4 xa[NRUN], xb[NRUN];
-  if (kb < ke) {
-    stage_load<!TA>(xa, g.A, g.lda, m0, g.M, kb, ke, g.vec_a != 0);
-    stage_load<TB>(xb, g.B, g.ldb, n0, g.N, kb, ke, g.vec_b != 0);
-  }
-  for (int k0 = kb; k0 < ke; k0 += TK) {
-    stage_store<!TA>(As, xa);
-    stage_store<TB>(Bs, xb);
-    __syncthreads();
-    if (k0 + TK < ke) {
-      stage_load<!TA>(xa, g.A, g.lda, m0, g.M, k0 + TK, ke, g.vec_a != 0);
-      stage_load<TB>(xb, g.B, g.ldb, n0, g.N, k0 + TK, ke, g.vec_b != 0);
+  bf16x4 xa[NRUN<T>], xb[NRUN<T>];
+  stage_load<T, !TA>(xa, g.A, g.lda, m0, g.M, 0, g.K, g.vec_a);
+  stage_load<T, TB>(xb, g.B, g.ldb, n0, g.N, 0, g.K, g.vec_b);
+  int kend = g.kchunk;              // of the current chunk
+#pragma unroll 1
+  for (int k0 = 0; k0 < g.K; k0 += TK) {
+    stage_store<T, !TA>(As, xa);
+    stage_store<T, TB>(Bs, xb);
+    lds_barrier();
+    if (k0 + TK < g.K) {
+      stage_load<T, !TA>(xa, g.A, g.lda, m0, g.M, k0 + TK, g.K, g.vec_a);
+      stage_load<T, TB>(xb, g.B, g.ldb, n0, g.N, k0 + TK, g.K, g.vec_b);
     }
     // lane l holds row/col (l % 32), k (l / 32) * 8 + j of each 32 x 32 x 16 step
 #pragma unroll
     for (int ks = 0; ks < TK; ks += 16) {
-      bf16x8 a[2], b[2];
+      bf16x8 a[NB], b[NB];
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
+      for (int i = 0; i < NB; ++i) {
         const int ra = wm + 32 * i + (lane & 31), rb = wn + 32 * i + (lane & 31);
         a[i] = *reinterpret_cast<const bf16x8*>(&As[ra][kswz(ra, ks + (lane >> 5) * 8)]);
         b[i] = *reinterpret_cast<const bf16x8*>(&Bs[rb][kswz(rb, ks + (lane >> 5) * 8)]);
       }
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < NB; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+        for (int j = 0; j < NB; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
     }
-    __syncthreads();
+    if (colsum) {
+#pragma unroll
+      for (int k = 0; k < TK; k += 8) {
+        const bf16x8 v = *reinterpret_cast<const bf16x8*>(&Bs[tid][kswz(tid, k)]);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) db += (float)v[j];
+      }
+    }
+    if (CHUNKS && (k0 + TK >= kend || k0 + TK >= g.K)) {
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) {
+            tot[i][j][e] += acc[i][j][e];
+            acc[i][j][e] = 0.0f;
+          }
+      kend += g.kchunk;
+    }
+    lds_barrier();
   }
   // ---- output: acc[i][j][e] is row (e / 4) * 8 + (l / 32) * 4 + e % 4 of block
   // i, column l % 32 of block j
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < NB; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
+    for (int j = 0; j < NB; ++j) {
+      const f32x16& c = CHUNKS ? tot[CHUNKS ? i : 0][CHUNKS ? j : 0] : acc[i][j];
       const int n = n0 + wn + 32 * j + (lane & 31);
+      const int mb = m0 + wm + 32 * i + (lane >> 5) * 4;
+      if (n >= g.N) continue;
+      if (!GRAD) {
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int m = m0 + wm + 32 * i + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
-        if (m < g.M && n < g.N) {
-          if (g.partial) g.outf[((size_t)blockIdx.z * g.M + m) * g.N + n] = acc[i][j][e];
-          else epilogue(g, m, n, acc[i][j][e]);
+        for (int e = 0; e < 16; ++e) {
+          const int m = mb + (e >> 2) * 8 + (e & 3);
+          if (m < g.M) epilogue(g, m, n, c[e]);
+        }
+      } else {
+#pragma unroll
+        for (int q = 0; q < 16; q += 8) {     // eight rows' loads in flight
+          float w[8], m1[8], m2[8];
+          if (g.gs.on) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              const int m = min(mb + ((q + e) >> 2) * 8 + (e & 3), g.M - 1);
+              const size_t o = (size_t)m * g.N + n;
+              w[e] = g.gs.W[o];
+              m1[e] = g.gs.mW[o];
+              m2[e] = g.gs.vW[o];
+            }
+          }
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const int m = mb + ((q + e) >> 2) * 8 + (e & 3);
+            if (m >= g.M) continue;
+            const size_t o = (size_t)m * g.N + n;
+            g.outf[o] = c[q + e];
+            if (g.gs.on) {
+              const float wi = adam_update(w[e], c[q + e], m1[e], m2[e], g.gs.a);
+              g.gs.W[o] = wi;
+              g.gs.Wb[o] = (__bf16)wi;
+              g.gs.mW[o] = m1[e];
+              g.gs.vW[o] = m2[e];
+            }
+          }
         }
       }
     }
+  if (colsum && n0 + tid < g.N) {
+    const int n = n0 + tid;
+    g.gs.db[n] = db;
+    if (g.gs.on) {
+      float m1 = g.gs.mb[n], m2 = g.gs.vb[n];
+      g.gs.b[n] = adam_update(g.gs.b[n], db, m1, m2, g.gs.a);
+      g.gs.mb[n] = m1;
+      g.gs.vb[n] = m2;
+    }
+  }
 }
 
-// sum the split-K partials in split order, then the epilogue
-__global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmArgs g, const float* part, int splits) {
-  const long total = (long)g.M * g.N;
-  for (long o = (long)blockIdx.x * 256 + threadIdx.x; o < total; o += (long)gridDim.x * 256) {
-    float s = 0.0f;
-    for (int z = 0; z < splits; ++z) s += part[(size_t)z * total + o];
-    epilogue(g, (int)(o / g.N), (int)(o % g.N), s);
+// 8 consecutive elements along k of a row, zero past `lim`
+__device__ __forceinline__ bf16x8 load_k8(const __bf16* src, int lim) {
+  bf16x8 v;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) v[j] = j < lim ? src[j] : (__bf16)0.0f;
+  return v;
+}
+
+// C tile of 32 x 32 with a chunk of K per wave, W waves a round; the chunks'
+// sums meet in LDS and are added in order.  The fragments are loaded in the
+// layout of the matrix instruction straight from memory: each is used once by
+// the workgroup, and the waves with U steps of loads each cover the latency,
+// so staging them would add a barrier per 64 of K and save nothing.
+// Rows and columns past the edge repeat the last one; their results are dropped.
+// A row of B gives a tile 64 bytes, half a line, so neighbouring tiles run on
+// one XCD (workgroups go to the eight XCDs in turn) and share it in the L2.
+template <bool TB, int W>
+__global__ __launch_bounds__(W * 64) void gemm_rows_kernel(GemmArgs g) {
+  constexpr int E = RT * RT / (W * 64), U = W == 1 ? 8 : 4;
+  __shared__ float part[W][RT * RT];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int bx = blockIdx.x, pair = bx & 15;
+  const int m0 = blockIdx.y * RT;
+  const int n0 = (bx - pair + 16 <= (int)gridDim.x ? bx - pair + (pair & 7) * 2 + (pair >> 3) : bx) * RT;
+  const int chunks = (g.K + g.kchunk - 1) / g.kchunk;
+  const __bf16* a_row = g.A + (size_t)min(m0 + (lane & 31), g.M - 1) * g.lda;
+  const int bn = min(n0 + (lane & 31), g.N - 1);
+  const __bf16* b_base = TB ? g.B + (size_t)bn * g.ldb : g.B + bn;
+  const int kl = (lane >> 5) * 8;
+  float tot[E] = {};
+  for (int c0 = blockIdx.z * W; c0 < chunks; c0 += gridDim.z * W) {
+    const int c = c0 + wv;
+    f32x16 acc = {};
+    if (c < chunks) {
+      const int ke = min(g.K, (c + 1) * g.kchunk);
+      int k0 = c * g.kchunk;
+      bf16x8 a[U], b[U];
+      const bool vec = g.vec_a && (!TB || g.vec_b);
+      for (; vec && k0 + 16 * U <= ke; k0 += 16 * U) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int k = k0 + 16 * u + kl;
+          a[u] = *reinterpret_cast<const bf16x8_a4*>(a_row + k);
+          if (!TB) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) b[u][j] = b_base[(size_t)(k + j) * g.ldb];
+          } else {
+            b[u] = *reinterpret_cast<const bf16x8_a4*>(b_base + k);
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[u], b[u], acc, 0, 0, 0);
+      }
+      for (; k0 < ke; k0 += 16) {
+        const int k = k0 + kl, lim = ke - k;
+        a[0] = load_k8(a_row + k, lim);
+        if (TB) {
+          b[0] = load_k8(b_base + k, lim);
+        } else {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) b[0][j] = j < lim ? b_base[(size_t)(k + j) * g.ldb] : (__bf16)0.0f;
+        }
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[0], acc, 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 16; ++e)
+      part[wv][((e >> 2) * 8 + (lane >> 5) * 4 + (e & 3)) * RT + (lane & 31)] = acc[e];
+    __syncthreads();
+    if (g.partial) {
+      for (int j = 0; j < min(W, chunks - c0); ++j)
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+          const int o = tid + e * W * 64, m = m0 + o / RT, n = n0 + o % RT;
+          if (m < g.M && n < g.N) g.outf[((size_t)(c0 + j) * g.M + m) * g.N + n] = part[j][o];
+        }
+    } else {
+      for (int j = 0; j < min(W, chunks - c0); ++j)
+#pragma unroll
+        for (int e = 0; e < E; ++e) tot[e] += part[j][tid + e * W * 64];
+    }
+    __syncthreads();
   }
+  if (g.partial) return;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int o = tid + e * W * 64, m = m0 + o / RT, n = n0 + o % RT;
+    if (m < g.M && n < g.N) epilogue(g, m, n, tot[e]);
+  }
+}
+
+// the chunks' sums added in order, then the epilogue; 16 loads in flight and
+// one wave a workgroup, since there are few outputs and many chunks (512
+// outputs of 114 chunks: 27 us with one load at a time on two workgroups)
+__global__ __launch_bounds__(64) void chunk_sum_kernel(GemmArgs g, const float* part, int chunks) {
+  const long total = (long)g.M * g.N, o = (long)blockIdx.x * 64 + threadIdx.x;
+  if (o >= total) return;
+  float s = 0.0f;
+  int z = 0;
+  for (; z + 16 <= chunks; z += 16) {
+    float v[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) v[j] = part[(size_t)(z + j) * total + o];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) s += v[j];
+  }
+  for (; z < chunks; ++z) s += part[(size_t)z * total + o];
+  epilogue(g, (int)(o / g.N), (int)(o % g.N), s);
 }
 
 __global__ __launch_bounds__(256) void to_bf16_kernel(const float* x, __bf16* y, long n) {
@@ -241,48 +451,28 @@ __global__ __launch_bounds__(64) void sum_partials_kernel(const double* part, in
   if (threadIdx.x == 0) out[0] = s;
 }
 
-// db[n] = sum over rows of dz[b][n] (FP32, rows in order; 8 loads in flight)
-__global__ __launch_bounds__(256) void colsum_kernel(const __bf16* dz, int rows, int N, float* db) {
-  const int n = blockIdx.x * 256 + threadIdx.x;
-  if (n >= N) return;
-  float s = 0.0f;
-  int b = 0;
-  for (; b + 8 <= rows; b += 8) {
-    float v[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) v[j] = (float)dz[(size_t)(b + j) * N + n];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) s += v[j];
-  }
-  for (; b < rows; ++b) s += (float)dz[(size_t)b * N + n];
-  db[n] = s;
-}
-
-__global__ __launch_bounds__(256) void adam_kernel(float* w, __bf16* wb, const float* g, float* m, float* v,
-                                                  long n, AdamStep a) {
-  for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < n; i += (long)gridDim.x * 256) {
-    const float gi = g[i];
-    const float mi = a.b1 * m[i] + a.omb1 * gi;
-    const float vi = a.b2 * v[i] + a.omb2 * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    const float wi = w[i] - a.lr * (mi / a.c1) / (sqrtf(vi / a.c2) + a.eps);
-    w[i] = wi;
-    if (wb) wb[i] = (__bf16)wi;
-  }
-}
-
 int grid_for(long n, int per, int cap) {
   long g = (n + per - 1) / per;
   return (int)std::max<long>(1, std::min<long>(g, cap));
 }
 
-}  // namespace
+// The chunks of a product's sum over K: as many (a power of two, in steps of
+// TK) as keep 128 x 128 tiles within three workgroups a CU and the chunks' sums
+// within `work_floats`.  This is the definition of the sum: it fixes the order
+// of the additions, whichever kernel carries them out.
+int chunk_k(int M, int N, int K, size_t work_floats) {
+  const int tiles = ((M + 127) / 128) * ((N + 127) / 128);
+  const int ksteps = std::max(1, (K + TK - 1) / TK);
+  int splits = 1;
+  while (tiles * splits * 2 <= 768 && splits * 2 <= ksteps &&
+         (size_t)(splits * 2) * (size_t)M * (size_t)N <= work_floats)
+    splits *= 2;
+  return (ksteps + splits - 1) / splits * TK;
+}
 
-hipError_t mlp_gemm(const __bf16* A, bool ta, long lda, const __bf16* B, bool tb, long ldb, int M, int N,
-                    int K, int epi, const float* bias, const __bf16* mask, float* outf, __bf16* outb,
-                    float* work, size_t work_floats, hipStream_t st) {
-  if (M <= 0 || N <= 0) return hipSuccess;
+GemmArgs gemm_args(const __bf16* A, bool ta, long lda, const __bf16* B, bool tb, long ldb, int M, int N, int K,
+                   int epi, size_t work_floats) {
+  const int ca = ta ? M : K, cb = tb ? K : N;   // contiguous dimensions
   GemmArgs g{};
   g.A = A;
   g.B = B;
@@ -292,42 +482,77 @@ hipError_t mlp_gemm(const __bf16* A, bool ta, long lda, const __bf16* B, bool tb
   g.N = N;
   g.K = K;
   g.epi = epi;
-  g.vec_a = (lda % VW == 0) ? 1 : 0;
-  g.vec_b = (ldb % VW == 0) ? 1 : 0;
+  g.vec_a = lda % 2 == 0 && ca % 2 == 0 && ca >= VW;
+  g.vec_b = ldb % 2 == 0 && cb % 2 == 0 && cb >= VW;
+  g.kchunk = chunk_k(M, N, K, work_floats);
+  return g;
+}
+
+template <bool TB>
+void launch_rows(const GemmArgs& g, dim3 grid, int chunks, hipStream_t st) {
+  if (chunks > 8) hipLaunchKernelGGL((gemm_rows_kernel<TB, 16>), grid, dim3(16 * 64), 0, st, g);
+  else if (chunks > 1) hipLaunchKernelGGL((gemm_rows_kernel<TB, 8>), grid, dim3(8 * 64), 0, st, g);
+  else hipLaunchKernelGGL((gemm_rows_kernel<TB, 1>), grid, dim3(64), 0, st, g);
+}
+
+template <bool TA, bool TB>
+void launch_staged(const GemmArgs& g, int chunks, hipStream_t st) {
+  const int T = chunks > 1 ? 64 : 128;
+  const dim3 grid((g.N + T - 1) / T, (g.M + T - 1) / T);
+  if (chunks > 1) hipLaunchKernelGGL((gemm_kernel<64, TA, TB>), grid, dim3(GT), 0, st, g);
+  else hipLaunchKernelGGL((gemm_kernel<128, TA, TB>), grid, dim3(GT), 0, st, g);
+}
+
+}  // namespace
+
+hipError_t mlp_gemm(const __bf16* A, long lda, const __bf16* B, bool tb, long ldb, int M, int N, int K, int epi,
+                    const float* bias, const __bf16* mask, float* outf, __bf16* outb, float* work,
+                    size_t work_floats, hipStream_t st) {
+  if (M <= 0 || N <= 0) return hipSuccess;
+  GemmArgs g = gemm_args(A, false, lda, B, tb, ldb, M, N, K, epi, work_floats);
   g.bias = bias;
   g.mask = mask;
   g.outf = outf;
   g.outb = outb;
-  const int tiles = ((M + TM - 1) / TM) * ((N + TN - 1) / TN);
-  // split K while the grid stays within one round of resident workgroups
-  // (three per CU) and the partials fit
-  const int ksteps = std::max(1, (K + TK - 1) / TK);
-  int splits = 1;
-  while (tiles * splits * 2 <= 768 && splits * 2 <= ksteps &&
-         (size_t)(splits * 2) * (size_t)M * (size_t)N <= work_floats)
-    splits *= 2;
-  const int per = (ksteps + splits - 1) / splits;
-  g.kchunk = per * TK;
-  splits = (ksteps + per - 1) / per;
-  dim3 grid((N + TN - 1) / TN, (M + TM - 1) / TM, splits);
-  if (splits > 1) {
-    g.partial = 1;
-    GemmArgs p = g;
-    p.outf = work;
-    if (!ta && !tb) hipLaunchKernelGGL((gemm_kernel<false, false>), grid, dim3(GT), 0, st, p);
-    else if (!ta && tb) hipLaunchKernelGGL((gemm_kernel<false, true>), grid, dim3(GT), 0, st, p);
-    else if (ta && !tb) hipLaunchKernelGGL((gemm_kernel<true, false>), grid, dim3(GT), 0, st, p);
-    else hipLaunchKernelGGL((gemm_kernel<true, true>), grid, dim3(GT), 0, st, p);
-    g.partial = 0;
-    hipLaunchKernelGGL(splitk_reduce_kernel, dim3(grid_for((long)M * N, 256, 4096)), dim3(256), 0, st, g,
-                       work, splits);
+  const int chunks = (K + g.kchunk - 1) / g.kchunk;
+  const long t64 = (long)((M + 63) / 64) * ((N + 63) / 64);
+  // a wave per chunk: up to 32 rows, of which a staged tile would hold mostly
+  // padding, and products of fewer than 400 64 x 64 tiles, about three waves a
+  // SIMD at most (256 x 5450 x 512, 344 tiles: 20 us, 22.5 staged; 256 x 512 x
+  // 4800, 32 tiles: 23 us, 25 through memory)
+  if (M <= RT || (chunks > 1 && t64 < 400)) {
+    dim3 grid((N + RT - 1) / RT, (M + RT - 1) / RT);
+    // fewer than 64 tiles: the chunks go to several workgroups as well
+    const bool spread = chunks > 16 && grid.x * grid.y < 64;
+    if (spread) {
+      GemmArgs p = g;
+      p.partial = 1;
+      p.outf = work;
+      grid.z = (chunks + 7) / 8;
+      if (tb) hipLaunchKernelGGL((gemm_rows_kernel<true, 8>), grid, dim3(8 * 64), 0, st, p);
+      else hipLaunchKernelGGL((gemm_rows_kernel<false, 8>), grid, dim3(8 * 64), 0, st, p);
+      hipLaunchKernelGGL(chunk_sum_kernel, dim3((unsigned)(((long)M * N + 63) / 64)), dim3(64), 0, st, g, work,
+                         chunks);
+    } else if (tb) {
+      launch_rows<true>(g, grid, chunks, st);
+    } else {
+      launch_rows<false>(g, grid, chunks, st);
+    }
+  } else if (tb) {
+    launch_staged<false, true>(g, chunks, st);
   } else {
-    g.partial = 0;
-    if (!ta && !tb) hipLaunchKernelGGL((gemm_kernel<false, false>), grid, dim3(GT), 0, st, g);
-    else if (!ta && tb) hipLaunchKernelGGL((gemm_kernel<false, true>), grid, dim3(GT), 0, st, g);
-    else if (ta && !tb) hipLaunchKernelGGL((gemm_kernel<true, false>), grid, dim3(GT), 0, st, g);
-    else hipLaunchKernelGGL((gemm_kernel<true, true>), grid, dim3(GT), 0, st, g);
+    launch_staged<false, false>(g, chunks, st);
   }
+  return hipGetLastError();
+}
+
+hipError_t mlp_grad(const __bf16* in, const __bf16* dz, int rows, int K, int N, float* dW, const GradStep& s,
+                    size_t work_floats, hipStream_t st) {
+  if (K <= 0 || N <= 0) return hipSuccess;
+  GemmArgs g = gemm_args(in, true, K, dz, false, N, K, N, rows, EPI_GRAD, work_floats);
+  g.outf = dW;
+  g.gs = s;
+  launch_staged<true, false>(g, (rows + g.kchunk - 1) / g.kchunk, st);
   return hipGetLastError();
 }
 
@@ -342,18 +567,6 @@ hipError_t mlp_mse_grad(const float* yhat, const float* y, __bf16* dz, long n, f
   const int grid = grid_for(n, 256, 1024);
   hipLaunchKernelGGL(mse_grad_kernel, dim3(grid), dim3(256), 0, st, yhat, y, dz, n, scale, part);
   hipLaunchKernelGGL(sum_partials_kernel, dim3(1), dim3(64), 0, st, part, grid, loss);
-  return hipGetLastError();
-}
-
-hipError_t mlp_colsum(const __bf16* dz, int rows, int N, float* db, hipStream_t st) {
-  hipLaunchKernelGGL(colsum_kernel, dim3((N + 255) / 256), dim3(256), 0, st, dz, rows, N, db);
-  return hipGetLastError();
-}
-
-hipError_t mlp_adam(float* w, __bf16* wb, const float* g, float* m, float* v, long n, const AdamStep& a,
-                    hipStream_t st) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(adam_kernel, dim3(grid_for(n, 256, 4096)), dim3(256), 0, st, w, wb, g, m, v, n, a);
   return hipGetLastError();
 }
 

@@ -14,7 +14,7 @@ using namespace pdhcg;
 
 namespace {
 
-constexpr size_t WORK_FLOATS = (size_t)16 << 20;   // split-K partials (64 MiB)
+constexpr size_t WORK_FLOATS = (size_t)16 << 20;   // sums of K's chunks (64 MiB)
 
 struct Layer {
   int K = 0, N = 0;
@@ -61,16 +61,17 @@ struct Mlp {
     if ((expr) != hipSuccess) return PDHCG_E_HIP; \
   } while (0)
 
-int forward(Mlp* h, const float* x, int B) {
+// the network's output goes to `out` (batch x dims[L])
+int forward(Mlp* h, const float* x, int B, float* out) {
   MCHK(mlp_to_bf16(x, h->X, (long)B * h->dims[0], h->st));
   for (int l = 0; l < h->L; ++l) {
     Layer& ly = h->layers[l];
     const __bf16* in = l == 0 ? h->X : h->H[l];
     if (l < h->L - 1)
-      MCHK(mlp_gemm(in, false, ly.K, ly.Wb, false, ly.N, B, ly.N, ly.K, EPI_BIAS_RELU_BF16, ly.b, nullptr,
+      MCHK(mlp_gemm(in, ly.K, ly.Wb, false, ly.N, B, ly.N, ly.K, EPI_BIAS_RELU_BF16, ly.b, nullptr,
                     nullptr, h->H[l + 1], h->work, WORK_FLOATS, h->st));
     else
-      MCHK(mlp_gemm(in, false, ly.K, ly.Wb, false, ly.N, B, ly.N, ly.K, EPI_BIAS_F32, ly.b, nullptr, h->Yhat,
+      MCHK(mlp_gemm(in, ly.K, ly.Wb, false, ly.N, B, ly.N, ly.K, EPI_BIAS_F32, ly.b, nullptr, out,
                     nullptr, h->work, WORK_FLOATS, h->st));
   }
   return PDHCG_OK;
@@ -186,10 +187,7 @@ int pdhcg_mlp_get_grads(void* hv, int32_t layer, float* dW, float* db) {
 int pdhcg_mlp_forward(void* hv, const float* x, int32_t batch, float* y) {
   Mlp* h = (Mlp*)hv;
   if (!h || !x || !y || batch < 1 || batch > h->max_batch) return PDHCG_E_ARG;
-  int rc = forward(h, x, batch);
-  if (rc != PDHCG_OK) return rc;
-  MCHK(hipMemcpyAsync(y, h->Yhat, (size_t)batch * h->dims[h->L] * 4, hipMemcpyDeviceToDevice, h->st));
-  return PDHCG_OK;
+  return forward(h, x, batch, y);
 }
 
 int pdhcg_mlp_train_step(void* hv, const float* x, const float* y, int32_t batch, const pdhcg_adam* opt,
@@ -197,28 +195,16 @@ int pdhcg_mlp_train_step(void* hv, const float* x, const float* y, int32_t batch
   Mlp* h = (Mlp*)hv;
   if (!h || !x || !y || batch < 1 || batch > h->max_batch) return PDHCG_E_ARG;
   const int B = batch, L = h->L, dL = h->dims[L];
-  int rc = forward(h, x, B);
+  int rc = forward(h, x, B, h->Yhat);
   if (rc != PDHCG_OK) return rc;
   int cur = 0;
   MCHK(mlp_mse_grad(h->Yhat, y, h->dz[cur], (long)B * dL, (float)(2.0 / ((double)B * dL)), h->part, h->dloss,
                     h->st));
-  for (int l = L - 1; l >= 0; --l) {
-    Layer& ly = h->layers[l];
-    const __bf16* in = h->H[l];     // H_{l} of the docs: the layer's input activations
-    // dW = in^T dz  (M = K_in, N = N_out, K = batch)
-    MCHK(mlp_gemm(in, true, ly.K, h->dz[cur], false, ly.N, ly.K, ly.N, B, EPI_F32, nullptr, nullptr, ly.dW,
-                  nullptr, h->work, WORK_FLOATS, h->st));
-    MCHK(mlp_colsum(h->dz[cur], B, ly.N, ly.db, h->st));
-    if (l > 0) {
-      // dz_prev = (dz W^T) masked by in > 0   (M = batch, N = K_in, K = N_out)
-      MCHK(mlp_gemm(h->dz[cur], false, ly.N, ly.Wb, true, ly.N, B, ly.K, ly.N, EPI_MASK_BF16, nullptr, in,
-                    nullptr, h->dz[1 - cur], h->work, WORK_FLOATS, h->st));
-      cur = 1 - cur;
-    }
-  }
+  GradStep gs{};
   if (opt) {
     h->t += 1;
-    AdamStep a;
+    gs.on = 1;
+    AdamStep& a = gs.a;
     a.lr = (float)opt->lr;
     a.b1 = (float)opt->beta1;
     a.b2 = (float)opt->beta2;
@@ -227,10 +213,27 @@ int pdhcg_mlp_train_step(void* hv, const float* x, const float* y, int32_t batch
     a.omb2 = (float)(1.0 - opt->beta2);
     a.c1 = (float)(1.0 - std::pow(opt->beta1, (double)h->t));
     a.c2 = (float)(1.0 - std::pow(opt->beta2, (double)h->t));
-    for (auto& ly : h->layers) {
-      MCHK(mlp_adam(ly.W, ly.Wb, ly.dW, ly.mW, ly.vW, (long)ly.K * ly.N, a, h->st));
-      MCHK(mlp_adam(ly.b, nullptr, ly.db, ly.mb, ly.vb, ly.N, a, h->st));
+  }
+  for (int l = L - 1; l >= 0; --l) {
+    Layer& ly = h->layers[l];
+    const __bf16* in = l == 0 ? h->X : h->H[l];
+    const __bf16* dz = h->dz[cur];
+    if (l > 0) {
+      // dz_prev = (dz W^T) masked by in > 0   (M = batch, N = K_in, K = N_out),
+      // before the step that changes W
+      MCHK(mlp_gemm(dz, ly.N, ly.Wb, true, ly.N, B, ly.K, ly.N, EPI_MASK_BF16, nullptr, in, nullptr, h->dz[1 - cur],
+                    h->work, WORK_FLOATS, h->st));
+      cur = 1 - cur;
     }
+    gs.W = ly.W;
+    gs.mW = ly.mW;
+    gs.vW = ly.vW;
+    gs.Wb = ly.Wb;
+    gs.b = ly.b;
+    gs.mb = ly.mb;
+    gs.vb = ly.vb;
+    gs.db = ly.db;
+    MCHK(mlp_grad(in, dz, B, ly.K, ly.N, ly.dW, gs, WORK_FLOATS, h->st));
   }
   if (loss) {
     double s = 0.0;
