@@ -8,14 +8,16 @@
 // The sum over K is cut into chunks (chunk_k below): a chunk is one chain of
 // v_mfma_f32_32x32x16_bf16 from zero, and the chunks' sums are added in order
 // to zero.  Three kernels form the same sums:
-//   gemm_kernel<128>  one chunk, tiles of 128 x 128 staged in LDS: large M x N
-//   gemm_kernel<64>   several chunks one after another, tiles of 64 x 64
+//   gemm_kernel<128>  tiles of 128 x 128 staged in LDS, one chunk: large M x N,
+//                     or long chunks
+//   gemm_kernel<64>   several chunks one after another, tiles of 64 x 64 (and
+//                     up to 64 rows)
 //   gemm_rows_kernel  a chunk per wave, tiles of 32 x 32, fragments straight
 //                     from memory: few tiles and long K, or up to 32 rows
-// so the chunks never travel through memory, except where a product has too
-// few tiles for the chip (one row): then they are spread over workgroups and
-// added by a second kernel.  As partial tiles in memory, one for each chunk,
-// they were 20 to 44 MB a product, written and read.
+// so the chunks do not travel through memory (as partial tiles they were 20 to
+// 44 MB a product, written and read), except where a product has too few tiles
+// for the chip (one row) or long chunks: then they are spread over workgroups
+// and added by a second kernel.
 //
 // In the staged kernels each of the four waves owns a quarter of the tile;
 // both operand tiles are staged with K contiguous (row stride padded by 8
@@ -42,6 +44,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 constexpr int TK = 64, LDK = TK + 8;
 constexpr int GT = 256;   // threads per staged GEMM workgroup (4 waves, 2 x 2)
 constexpr int RT = 32;    // tile of gemm_rows_kernel
+constexpr int KROWS = 6000;   // mlp_gemm
 constexpr int VW = 4;     // elements per vector load (8 bytes)
 
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
@@ -190,7 +193,7 @@ __device__ __forceinline__ void lds_barrier() {
 // is taken where the gradient is: dW, W, m and v pass through memory once
 // (512 x 5450 x 256: 24 us, bound by those 84 MB; 57 us in five kernels).
 template <int T, bool TA, bool TB>
-__global__ __launch_bounds__(GT) void gemm_kernel(GemmArgs g) {
+__global__ __launch_bounds__(GT, T == 64 ? 3 : 2) void gemm_kernel(GemmArgs g) {
   constexpr bool CHUNKS = T == 64;
   constexpr int NB = T / 64;        // 32 x 32 blocks per wave and direction
   __shared__ __attribute__((aligned(16))) __bf16 As[T][LDK];
@@ -204,15 +207,16 @@ __global__ __launch_bounds__(GT) void gemm_kernel(GemmArgs g) {
   f32x16 acc[NB][NB] = {}, tot[CHUNKS ? NB : 1][CHUNKS ? NB : 1] = {};
   // the next stage's global loads are in flight while this stage computes
   bf16x4 xa[NRUN<T>], xb[NRUN<T>];
-  stage_load<T, !TA>(xa, g.A, g.lda, m0, g.M, 0, g.K, g.vec_a);
-  stage_load<T, TB>(xb, g.B, g.ldb, n0, g.N, 0, g.K, g.vec_b);
+  const int kb = CHUNKS ? 0 : blockIdx.z * g.kchunk, ke = CHUNKS ? g.K : min(g.K, kb + g.kchunk);
+  stage_load<T, !TA>(xa, g.A, g.lda, m0, g.M, kb, g.K, g.vec_a);
+  stage_load<T, TB>(xb, g.B, g.ldb, n0, g.N, kb, g.K, g.vec_b);
   int kend = g.kchunk;              // of the current chunk
 #pragma unroll 1
-  for (int k0 = 0; k0 < g.K; k0 += TK) {
+  for (int k0 = kb; k0 < ke; k0 += TK) {
     stage_store<T, !TA>(As, xa);
     stage_store<T, TB>(Bs, xb);
     lds_barrier();
-    if (k0 + TK < g.K) {
+    if (k0 + TK < ke) {
       stage_load<T, !TA>(xa, g.A, g.lda, m0, g.M, k0 + TK, g.K, g.vec_a);
       stage_load<T, TB>(xb, g.B, g.ldb, n0, g.N, k0 + TK, g.K, g.vec_b);
     }
@@ -268,7 +272,9 @@ __global__ __launch_bounds__(GT) void gemm_kernel(GemmArgs g) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
           const int m = mb + (e >> 2) * 8 + (e & 3);
-          if (m < g.M) epilogue(g, m, n, c[e]);
+          if (m >= g.M) continue;
+          if (!CHUNKS && g.partial) g.outf[((size_t)blockIdx.z * g.M + m) * g.N + n] = c[e];
+          else epilogue(g, m, n, c[e]);
         }
       } else {
 #pragma unroll
@@ -497,9 +503,11 @@ void launch_rows(const GemmArgs& g, dim3 grid, int chunks, hipStream_t st) {
 
 template <bool TA, bool TB>
 void launch_staged(const GemmArgs& g, int chunks, hipStream_t st) {
-  const int T = chunks > 1 ? 64 : 128;
-  const dim3 grid((g.N + T - 1) / T, (g.M + T - 1) / T);
-  if (chunks > 1) hipLaunchKernelGGL((gemm_kernel<64, TA, TB>), grid, dim3(GT), 0, st, g);
+  // the chunks one after another; also for up to 64 rows, half of a tile of 128
+  const bool inside = !g.partial && (chunks > 1 || g.M <= 64);
+  const int T = inside ? 64 : 128;
+  const dim3 grid((g.N + T - 1) / T, (g.M + T - 1) / T, inside ? 1 : chunks);
+  if (inside) hipLaunchKernelGGL((gemm_kernel<64, TA, TB>), grid, dim3(GT), 0, st, g);
   else hipLaunchKernelGGL((gemm_kernel<128, TA, TB>), grid, dim3(GT), 0, st, g);
 }
 
@@ -519,30 +527,32 @@ hipError_t mlp_gemm(const __bf16* A, long lda, const __bf16* B, bool tb, long ld
   // a wave per chunk: up to 32 rows, of which a staged tile would hold mostly
   // padding, and products of fewer than 400 64 x 64 tiles, about three waves a
   // SIMD at most (256 x 5450 x 512, 344 tiles: 20 us, 22.5 staged; 256 x 512 x
-  // 4800, 32 tiles: 23 us, 25 through memory)
-  if (M <= RT || (chunks > 1 && t64 < 400)) {
-    dim3 grid((N + RT - 1) / RT, (M + RT - 1) / RT);
-    // fewer than 64 tiles: the chunks go to several workgroups as well
-    const bool spread = chunks > 16 && grid.x * grid.y < 64;
-    if (spread) {
-      GemmArgs p = g;
-      p.partial = 1;
-      p.outf = work;
-      grid.z = (chunks + 7) / 8;
-      if (tb) hipLaunchKernelGGL((gemm_rows_kernel<true, 8>), grid, dim3(8 * 64), 0, st, p);
-      else hipLaunchKernelGGL((gemm_rows_kernel<false, 8>), grid, dim3(8 * 64), 0, st, p);
-      hipLaunchKernelGGL(chunk_sum_kernel, dim3((unsigned)(((long)M * N + 63) / 64)), dim3(64), 0, st, g, work,
-                         chunks);
-    } else if (tb) {
-      launch_rows<true>(g, grid, chunks, st);
-    } else {
-      launch_rows<false>(g, grid, chunks, st);
-    }
-  } else if (tb) {
-    launch_staged<false, true>(g, chunks, st);
-  } else {
-    launch_staged<false, false>(g, chunks, st);
+  // 4800, 32 tiles: 23 us, 25 through memory).  Tiles of 32 read A and B from
+  // the L2 four times as often as tiles of 128, so beyond KROWS the staged
+  // tiles win although their sums travel (forward pass of 13670-512-512-923 at
+  // batch 128: 75 us in tiles of 32, 37 staged)
+  const bool rows = M <= RT || (chunks > 1 && t64 < 400 && K <= KROWS);
+  dim3 grid((N + RT - 1) / RT, (M + RT - 1) / RT);
+  // fewer than 64 tiles of 32 x 32: the chunks go to several workgroups as well
+  const bool spread = rows ? chunks > 16 && grid.x * grid.y < 64 : chunks > 1 && t64 < 400;
+  GemmArgs p = g;
+  if (spread) {
+    p.partial = 1;
+    p.outf = work;
   }
+  if (rows && spread) {
+    grid.z = (chunks + 7) / 8;
+    if (tb) hipLaunchKernelGGL((gemm_rows_kernel<true, 8>), grid, dim3(8 * 64), 0, st, p);
+    else hipLaunchKernelGGL((gemm_rows_kernel<false, 8>), grid, dim3(8 * 64), 0, st, p);
+  } else if (rows) {
+    if (tb) launch_rows<true>(g, grid, chunks, st);
+    else launch_rows<false>(g, grid, chunks, st);
+  } else {
+    if (tb) launch_staged<false, true>(p, chunks, st);
+    else launch_staged<false, false>(p, chunks, st);
+  }
+  if (spread)
+    hipLaunchKernelGGL(chunk_sum_kernel, dim3((unsigned)(((long)M * N + 63) / 64)), dim3(64), 0, st, g, work, chunks);
   return hipGetLastError();
 }
 

@@ -2171,9 +2171,11 @@ static const void* solver_kernel_for(int res, bool qdiag, bool fp32, bool ext, b
   return cones ? (const void*)solve_kernel : (const void*)solve_kernel_lin;
 }
 
-// dynamic LDS beyond 64 KiB has to be asked for
+// dynamic LDS beyond 64 KiB has to be asked for; always for the same size,
+// since the attribute belongs to the kernel and not to this launch
 static hipError_t allow_lds(const void* k, int bytes) {
-  return bytes > 0 ? hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) : hipSuccess;
+  return bytes > 64 * 1024 ? hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)RES_LDS_DYN)
+                           : hipSuccess;
 }
 
 hipError_t launch_solve(const KArgs& args, bool fp32, int grid, hipStream_t stream) {
