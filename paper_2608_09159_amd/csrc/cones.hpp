@@ -118,10 +118,14 @@ __device__ __forceinline__ double rcp_step(double x) {
   return y * (2.0 - x * y);
 }
 
-// A Newton step of size `step` from a point of size `at`, the one before it
-// of size `prev`: small enough, and shrinking fast enough, for the next one
-// to be below the resolution of the point (steps shrink quadratically: the
-// next is about step^3 / prev^2, at most 1e-15 of `at`)
+// A Newton step of size `step` from a point of size `at`, the Newton step
+// before it of size `prev`: small enough, and shrinking fast enough, for the
+// next one to be below the resolution of the point (steps shrink
+// quadratically: the next is about step^3 / prev^2, at most 1e-15 of `at`).
+// prev = 0 where no Newton step has gone before: a small step alone says
+// nothing about the curvature, which for a metric that spreads over 1e6 in an
+// SOC block leaves an error of 4e-7 ||r|| after a step of 1e-9 from the
+// previous root (1e-11 with one more).
 __device__ __forceinline__ bool newton_done(double step, double prev, double at) {
   return step <= 1e-9 * at && step <= 1e-3 * prev;
 }
@@ -233,22 +237,23 @@ __device__ SocSol soc_wave_solve(const In& in, bool euclid, double* warm, int Lg
     if (w0 > lo && w0 < hi) d = w0;
     else if (tE > 0.0 && mt * art / tE > lo && mt * art / tE < hi) d = mt * art / tE;
   }
-  double prev = INFINITY;
+  double prev = 0.0;
   for (int it = 0; it < 400; ++it) {
     eval(d, psi, dpsi);
     if (psi < 0.0) lo = d; else hi = d;
     if (psi == 0.0) break;
     double dn = d - psi * rcp_step(dpsi);
-    // converged: the Newton correction is below the resolution of d, or the
-    // next one would be (tested before the bracket test, since a converged
-    // step may land on the bracket end it has just set)
+    // converged: the Newton correction is below the resolution of d (tested
+    // before the bracket test, since a converged step may land on the bracket
+    // end it has just set), or the next one would be
     const double st = fabs(dn - d);
-    if (st <= 4.0 * 2.220446049250313e-16 * d || newton_done(st, prev, d)) {
+    const bool in_bracket = dn > lo && dn < hi;
+    if (st <= 4.0 * 2.220446049250313e-16 * d || (in_bracket && newton_done(st, prev, d))) {
       d = dn;
       break;
     }
-    prev = st;
-    if (!(dn > lo && dn < hi)) dn = isfinite(hi) ? 0.5 * (lo + hi) : 2.0 * fmax(d, lo);
+    prev = in_bracket ? st : 0.0;
+    if (!in_bracket) dn = isfinite(hi) ? 0.5 * (lo + hi) : 2.0 * fmax(d, lo);
     if (isfinite(hi) && hi - lo <= 4.0 * 2.220446049250313e-16 * hi) {
       d = dn;
       break;
@@ -601,7 +606,7 @@ __device__ __forceinline__ bool exp_point_if(const ExpData& e, double rho, doubl
 // of points drawn around the cone, and their wave searched for them in full;
 // with it 0.1% (400,000 blocks, 372 to 92 us).  false: not found.
 __device__ bool exp_newton(const ExpData& e, double rho, double out[3], double* warm) {
-  double lo = -INFINITY, hi = INFINITY, prev = INFINITY, grow = 1.0;
+  double lo = -INFINITY, hi = INFINITY, prev = 0.0, grow = 1.0;
   for (int it = 0; it < 60; ++it) {
     // H, dH, psi - t0 and N, all divided by e^(2 rho) resp. e^rho for rho > 0
     const double A = e.mr * e.r0 * (rho - 1.0) + e.ms * e.s0;
@@ -641,14 +646,15 @@ __device__ bool exp_newton(const ExpData& e, double rho, double out[3], double* 
     else hi = fmin(hi, rho);
     double rn = ok && dH > 0.0 ? rho - H * rcp_step(dH) : NAN;
     const double st = fabs(rn - rho), at = fmax(1.0, fabs(rho));
-    if (ok && (st <= 4.0 * 2.220446049250313e-16 * at || newton_done(st, prev, at))) {
+    const bool in_bracket = rn > lo && rn < hi;
+    if (ok && (st <= 4.0 * 2.220446049250313e-16 * at || (in_bracket && newton_done(st, prev, at)))) {
       if (!exp_point_if(e, rn, out)) return false;
       if (warm) *warm = rn;
       return true;
     }
     prev = st;
-    if (!(rn > lo && rn < hi)) {
-      prev = INFINITY;
+    if (!in_bracket) {
+      prev = 0.0;
       if (isfinite(lo) && isfinite(hi)) {
         if (hi - lo <= 8.9e-16 * at) return false;
         rn = 0.5 * (lo + hi);
@@ -788,7 +794,7 @@ __device__ __forceinline__ void project_pow_body(double x, double y, double z, d
   // and steps fell back to bisection: 14.6 evaluations from a cold start, up
   // to 50, and 3.5 / 23 from the previous root, against 4.4 / 10 and 2.6 / 5),
   // and in which rho and R - rho have no cancellation.
-  double t = 0.0, lo = -INFINITY, hi = INFINITY, prev = INFINITY, grow = 4.0;
+  double t = 0.0, lo = -INFINITY, hi = INFINITY, prev = 0.0, grow = 4.0;
   if (warm && fabs(*warm) <= 700.0) t = *warm;
   const double iR = 1.0 / R;
   double rho = 0.0, sig = 0.0;              // rho, R - rho
@@ -814,15 +820,16 @@ __device__ __forceinline__ void project_pow_body(double x, double y, double z, d
     else break;
     double tn = (isfinite(g) && dg < 0.0) ? t - g * rcp_step(dg) : NAN;
     const double st = fabs(tn - t), at = fmax(1.0, fabs(t));
-    if (st <= 2.0 * 2.220446049250313e-16 * at || newton_done(st, prev, at)) {   // converged
+    const bool in_bracket = tn > lo && tn < hi;
+    if (st <= 2.0 * 2.220446049250313e-16 * at || (in_bracket && newton_done(st, prev, at))) {   // converged
       t = tn;
       break;
     }
     prev = st;
     const bool closed = isfinite(lo) && isfinite(hi);
     // g_M levels off towards both ends, where a Newton step would run away
-    if (!(tn > lo && tn < hi) || (!closed && st > grow)) {
-      prev = INFINITY;
+    if (!in_bracket || (!closed && st > grow)) {
+      prev = 0.0;
       if (closed) {
         if (hi - lo <= 2.0 * 2.220446049250313e-16 * at) break;
         tn = 0.5 * (lo + hi);
@@ -877,7 +884,7 @@ __device__ __forceinline__ void project_exp1_body(double z0, double t0, double m
   // e^(2z) term dominates)
   hi = fmin(hi, log(fmax(t0, 0.0) + sqrt((mz / mt) * (z0 - lo))));
   if (hi < lo) hi = lo;
-  double z = hi, prev = INFINITY;
+  double z = hi, prev = 0.0;
   const double tol = 1e-15 * fmax(1.0, fabs(hi));
   for (int it = 0; it < 2000 && hi - lo > tol; ++it) {
     const double fz = exp1_f(z, z0, t0, mz, mt, d);
@@ -886,11 +893,12 @@ __device__ __forceinline__ void project_exp1_body(double z0, double t0, double m
     else { lo = hi = z; break; }
     double zn = (d > 0.0) ? z - fz * rcp_step(d) : 0.5 * (lo + hi);
     const double st = fabs(zn - z), at = fmax(1.0, fabs(z));
-    if (st <= 2.220446049250313e-16 * at || newton_done(st, prev, at)) { lo = hi = zn; break; }   // converged
+    const bool in_bracket = zn > lo && zn < hi;
+    if (st <= 2.220446049250313e-16 * at || (in_bracket && newton_done(st, prev, at))) { lo = hi = zn; break; }   // converged
     prev = st;
-    if (!(zn > lo && zn < hi)) {
+    if (!in_bracket) {
       zn = 0.5 * (lo + hi);
-      prev = INFINITY;
+      prev = 0.0;
     }
     z = zn;
   }
