@@ -204,7 +204,10 @@ typedef struct {
     void*   stream;               /* hipStream_t                              */
     int32_t verbose;              /* bit 0: a progress line on stderr per
                                      launch (at most every 5 s) in
-                                     pdhcg_solve                             */
+                                     pdhcg_solve; bit 4, for tests: workgroups
+                                     wait for each other for one clock tick
+                                     instead of 4 s, so a solve on several
+                                     workgroups ends as PDHCG_ABORTED        */
     int32_t time_kernels;         /* 1: time every solver launch with HIP
                                      events on `stream` (result.kernel_s)     */
     int32_t autotune;             /* batches: 1 = choose the lanes-per-row

@@ -89,7 +89,7 @@ struct Instance {
   DevBuf mem;
   DevProblem P{};
   DevVec V{};
-  Ctl* ctl = nullptr;
+  CtlBlock* ctl = nullptr;
   unsigned long long* comm = nullptr;   // the grid's exchange words (Comm), cleared before epoch 1
   unsigned epoch = 0;          // all-reduces done on them
   TraceBufs T{};
@@ -394,7 +394,7 @@ int upload_instance(Handle* h, Instance* I) {
     V.Axb = B.alloc<double>(m);
   }
   I->scratch = B.alloc<double>(2048 + 2);
-  I->ctl = B.alloc<Ctl>(1);
+  I->ctl = B.alloc<CtlBlock>(1);
   if (h->s.trace_iters > 0) {
     long cap = h->s.trace_iters;
     I->T.cap = (int)cap;
@@ -856,7 +856,7 @@ int upload_instance(Handle* h, Instance* I) {
       }
     }
   }
-  I->comm_bytes = sizeof(unsigned long long) * (COMM_HEAD + 2 * SL_COUNT * ((size_t)G + COMM_COPIES));
+  I->comm_bytes = sizeof(unsigned long long) * 2 * SL_COUNT * ((size_t)G + COMM_COPIES);
   I->comm = (unsigned long long*)B.alloc<char>(I->comm_bytes);
   I->d_perm = H.perm.empty() ? nullptr : B.upload(H.perm);
   I->io = B.alloc<double>(IO_DOUBLES);
@@ -1539,7 +1539,8 @@ int pdhcg_setup(const pdhcg_problem* probs, int32_t count, const pdhcg_settings*
   }
   if (rate_khz <= 0) rate_khz = 100000;
   h->rate_khz = rate_khz;
-  h->spin_limit = (unsigned long long)rate_khz * 1000ull * 4ull;   // 4 s
+  // 4 s; one tick for tests of PDHCG_ABORTED
+  h->spin_limit = s->verbose & 16 ? 1ull : (unsigned long long)rate_khz * 1000ull * 4ull;
   if (count > 1) {
     h->B = new (std::nothrow) Batch();
     if (!h->B) { pdhcg_free(h); return PDHCG_E_MEM; }
@@ -1604,18 +1605,18 @@ int pdhcg_solve(pdhcg_handle* h, const double* x0, const double* y0, pdhcg_resul
   } else {
     HIPCHK(launch_fill(I->V.y, m, 0.0, st));
   }
-  Ctl c0;
-  std::memset(&c0, 0, sizeof(c0));
+  CtlBlock cb;
+  std::memset(&cb, 0, sizeof(cb));
   HIPCHK(reset_cone_failure(st));
-  HIPCHK(hipMemcpyAsync(I->ctl, &c0, sizeof(c0), hipMemcpyHostToDevice, st));
+  HIPCHK(hipMemcpyAsync(I->ctl, &cb, sizeof(cb), hipMemcpyHostToDevice, st));
   HIPCHK(launch_fill(I->V.warm, I->n_warm, NAN, st));
   KArgs a{};
   a.P = I->P;
   a.V = I->V;
   a.S = h->ds;
-  a.ctl = I->ctl;
-  a.comm.abort = (int*)I->comm;
-  a.comm.out = I->comm + COMM_HEAD;
+  a.ctl = &I->ctl->c;
+  a.comm.abort = &I->ctl->abort;
+  a.comm.out = I->comm;
   a.comm.in = a.comm.out + 2 * SL_COUNT * COMM_COPIES;
   a.T = I->T;
   a.spin_limit = h->spin_limit;
@@ -1631,7 +1632,7 @@ int pdhcg_solve(pdhcg_handle* h, const double* x0, const double* y0, pdhcg_resul
     HIPCHK(hipMemsetAsync(dpt, 0, sizeof(unsigned long long) * PT_COUNT * I->grid, st));
   }
   a.ptimes = dpt;
-  Ctl c = c0;
+  Ctl& c = cb.c;
   int status = 0;
   const long long maxit = h->s.max_iter;
   // FP32 mode: FP32 bulk sweeps until the looser tolerance fp32_tol, then an
@@ -1663,8 +1664,9 @@ int pdhcg_solve(pdhcg_handle* h, const double* x0, const double* y0, pdhcg_resul
     if (timing) HIPCHK(hipEventRecord(ev0, st));
     HIPCHK(launch_solve(a, phase32, I->grid, st));
     if (timing) HIPCHK(hipEventRecord(ev1, st));
-    HIPCHK(hipMemcpyAsync(&c, I->ctl, sizeof(c), hipMemcpyDeviceToHost, st));
+    HIPCHK(hipMemcpyAsync(&cb, I->ctl, sizeof(cb), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
+    c.status = launch_status(cb);
     if (c.status != PDHCG_ABORTED) I->epoch = c.epoch;
     ++nlaunch;
     if (timing) {
@@ -1681,7 +1683,7 @@ int pdhcg_solve(pdhcg_handle* h, const double* x0, const double* y0, pdhcg_resul
       c.status = 0;
       c.started = 0;
       c.resume = 1;
-      HIPCHK(hipMemcpyAsync(I->ctl, &c, sizeof(c), hipMemcpyHostToDevice, st));
+      HIPCHK(hipMemcpyAsync(I->ctl, &cb, sizeof(cb), hipMemcpyHostToDevice, st));
       HIPCHK(hipStreamSynchronize(st));
       phase32 = false;
       a.S.tol = h->s.tol;
@@ -1925,7 +1927,7 @@ int pdhcg_get_trace(pdhcg_handle* h, int32_t inst, pdhcg_trace* t) {
   if (!h || !t || inst < 0 || inst >= (int)h->inst.size()) return PDHCG_E_ARG;
   Instance* I = h->inst[inst];
   const TraceBufs& T = h->B ? h->B->desc[inst].T : I->T;
-  const Ctl* dctl = h->B ? h->B->desc[inst].ctl : I->ctl;
+  const Ctl* dctl = h->B ? h->B->desc[inst].ctl : &I->ctl->c;
   if (T.cap <= 0) return PDHCG_E_NOTRACE;
   Ctl c;
   if (hipMemcpy(&c, dctl, sizeof(c), hipMemcpyDeviceToHost) != hipSuccess) return PDHCG_E_HIP;

@@ -166,14 +166,23 @@ struct TraceBufs {
   double *sc;                    // cap * 8 scalars
 };
 
-// what the workgroups of a grid exchange (one allocation): the abort word, one
-// pair of words per slot and workgroup for its partial, and COMM_COPIES
-// copies of one pair per slot for the totals.  A pair carries the two halves
-// of a double, each beside the epoch of the all-reduce that wrote it.
+// what a launch on one problem leaves for the host: the scalar state, and on
+// a line of its own the abort word of the grid
+struct CtlBlock {
+  Ctl c;
+  alignas(128) int abort;   // a workgroup's wait ended without its data
+};
+
+// the status of a launch: no workgroup may have left it on its own
+inline int launch_status(const CtlBlock& b) { return b.abort != 0 ? PDHCG_ABORTED : b.c.status; }
+
+// what the workgroups of a grid exchange (one allocation): COMM_COPIES copies
+// of one pair of words per slot for the totals, and one pair per slot and
+// workgroup for its partial.  A pair carries the two halves of a double, each
+// beside the epoch of the all-reduce that wrote it.
 constexpr int COMM_COPIES = 4;
-constexpr int COMM_HEAD = 16;        // words before the totals (the abort word's line)
 struct Comm {
-  int* abort;
+  int* abort;                // CtlBlock::abort
   unsigned long long* in;    // [SL_COUNT][G][2]
   unsigned long long* out;   // [COMM_COPIES][SL_COUNT][2]
 };
