@@ -11,7 +11,7 @@
 //   gemm_kernel<128>  tiles of 128 x 128 staged in LDS, one chunk: large M x N,
 //                     or long chunks
 //   gemm_kernel<64>   several chunks one after another, tiles of 64 x 64 (and
-//                     up to 64 rows)
+//                     one chunk where tiles of 128 leave the chip idle)
 //   gemm_rows_kernel  a chunk per wave, tiles of 32 x 32, fragments straight
 //                     from memory: few tiles and long K, or up to 32 rows
 // so the chunks do not travel through memory (as partial tiles they were 20 to
@@ -107,10 +107,14 @@ static_assert((64 / 4) * (TK / 4) / GT * 4 == NRUN<64>, "both staging forms use 
 // dimension are even and at least 4, so every run of 4 is one load, at the
 // matrix's last 4 elements where it would pass the end (by 2, or altogether).
 // No branches: as tests around each load they were most of a stage's time.
-template <int T, bool KCONTIG>
+// LEAN: the addresses are formed at each stage (the thread's index is opaque)
+// instead of kept in registers over the loop: 164 registers instead of 203 at
+// T = 128, so three workgroups a CU instead of two.
+template <int T, bool KCONTIG, bool LEAN>
 __device__ __forceinline__ void stage_load(bf16x4 (&x)[NRUN<T>], const __bf16* P, long ld, int r0, int rmax,
                                            int k0, int kend, bool vec) {
-  const int tid = threadIdx.x;
+  int tid = threadIdx.x;
+  if (LEAN) asm volatile("" : "+v"(tid));
   const __bf16 z = (__bf16)0.0f;
   constexpr int RUNS = TK / VW, RB = T / 4;
   if (vec) {
@@ -192,8 +196,10 @@ __device__ __forceinline__ void lds_barrier() {
 // B (the bias gradient) from the staged tiles, in row order, and the Adam step
 // is taken where the gradient is: dW, W, m and v pass through memory once
 // (512 x 5450 x 256: 24 us, bound by those 84 MB; 57 us in five kernels).
-template <int T, bool TA, bool TB>
-__global__ __launch_bounds__(GT, T == 64 ? 3 : 2) void gemm_kernel(GemmArgs g) {
+// PER: workgroups a CU.
+template <int T, bool TA, bool TB, int PER>
+__global__ __launch_bounds__(GT, PER) void gemm_kernel(GemmArgs g) {
+  constexpr bool LEAN = T == 128 && PER == 3;
   constexpr bool CHUNKS = T == 64;
   constexpr int NB = T / 64;        // 32 x 32 blocks per wave and direction
   __shared__ __attribute__((aligned(16))) __bf16 As[T][LDK];
@@ -208,8 +214,8 @@ __global__ __launch_bounds__(GT, T == 64 ? 3 : 2) void gemm_kernel(GemmArgs g) {
   // the next stage's global loads are in flight while this stage computes
   bf16x4 xa[NRUN<T>], xb[NRUN<T>];
   const int kb = CHUNKS ? 0 : blockIdx.z * g.kchunk, ke = CHUNKS ? g.K : min(g.K, kb + g.kchunk);
-  stage_load<T, !TA>(xa, g.A, g.lda, m0, g.M, kb, g.K, g.vec_a);
-  stage_load<T, TB>(xb, g.B, g.ldb, n0, g.N, kb, g.K, g.vec_b);
+  stage_load<T, !TA, LEAN>(xa, g.A, g.lda, m0, g.M, kb, g.K, g.vec_a);
+  stage_load<T, TB, LEAN>(xb, g.B, g.ldb, n0, g.N, kb, g.K, g.vec_b);
   int kend = g.kchunk;              // of the current chunk
 #pragma unroll 1
   for (int k0 = kb; k0 < ke; k0 += TK) {
@@ -217,8 +223,8 @@ __global__ __launch_bounds__(GT, T == 64 ? 3 : 2) void gemm_kernel(GemmArgs g) {
     stage_store<T, TB>(Bs, xb);
     lds_barrier();
     if (k0 + TK < ke) {
-      stage_load<T, !TA>(xa, g.A, g.lda, m0, g.M, k0 + TK, g.K, g.vec_a);
-      stage_load<T, TB>(xb, g.B, g.ldb, n0, g.N, k0 + TK, g.K, g.vec_b);
+      stage_load<T, !TA, LEAN>(xa, g.A, g.lda, m0, g.M, k0 + TK, g.K, g.vec_a);
+      stage_load<T, TB, LEAN>(xb, g.B, g.ldb, n0, g.N, k0 + TK, g.K, g.vec_b);
     }
     // lane l holds row/col (l % 32), k (l / 32) * 8 + j of each 32 x 32 x 16 step
 #pragma unroll
@@ -501,14 +507,34 @@ void launch_rows(const GemmArgs& g, dim3 grid, int chunks, hipStream_t st) {
   else hipLaunchKernelGGL((gemm_rows_kernel<TB, 1>), grid, dim3(64), 0, st, g);
 }
 
+// Which tile: 64 x 64 for several chunks one after another.  One chunk:
+//  - tiles of 64 for up to 64 rows, and where tiles of 128 are no more than
+//    the CUs (64 x 512, 256 rows: 14 and 9 us a pass);
+//  - else tiles of 128, which read the operands half as often, three a CU
+//    where that takes fewer turns of the chip than two a CU (output layer of
+//    512 x 49000, 256 rows, 766 tiles: 83 us a forward pass of
+//    600-512-512-49000 at two a CU, 65 at three);
+//  - but tiles of 64 where tiles of 128 take a second turn at two a CU and
+//    the small ones, four a CU, finish in at most one turn more than three
+//    large ones a CU: a turn of them takes 23 us, one of two or three large
+//    ones 37 or 50.  That is where the last row of tiles is half empty
+//    (512 x 33000, 160 rows: 75 us at two a CU, 59 in tiles of 64; 512 x
+//    40000: 72 and 48).  From 960 tiles of 128 on they lose (512 x 65000,
+//    129 rows, 1,016 tiles: 80 and 85).
 template <bool TA, bool TB>
 void launch_staged(const GemmArgs& g, int chunks, hipStream_t st) {
-  // the chunks one after another; also for up to 64 rows, half of a tile of 128
-  const bool inside = !g.partial && (chunks > 1 || g.M <= 64);
+  constexpr long CUS = 256;
+  const long t128 = (long)((g.N + 127) / 128) * ((g.M + 127) / 128);
+  const long t64 = (long)((g.N + 63) / 64) * ((g.M + 63) / 64);
+  const auto turns = [](long tiles, long per) { return (tiles + per * CUS - 1) / (per * CUS); };
+  const bool small = g.M <= 64 || (!TA && (t128 <= CUS || (t128 > 2 * CUS && t128 <= 15 * CUS / 4 &&
+                                                           turns(t64, 4) <= turns(t128, 3) + 1)));
+  const bool inside = !g.partial && (chunks > 1 || small);
   const int T = inside ? 64 : 128;
   const dim3 grid((g.N + T - 1) / T, (g.M + T - 1) / T, inside ? 1 : chunks);
-  if (inside) hipLaunchKernelGGL((gemm_kernel<64, TA, TB>), grid, dim3(GT), 0, st, g);
-  else hipLaunchKernelGGL((gemm_kernel<128, TA, TB>), grid, dim3(GT), 0, st, g);
+  if (inside) hipLaunchKernelGGL((gemm_kernel<64, TA, TB, 3>), grid, dim3(GT), 0, st, g);
+  else if (!g.partial && turns(t128, 3) < turns(t128, 2)) hipLaunchKernelGGL((gemm_kernel<128, TA, TB, 3>), grid, dim3(GT), 0, st, g);
+  else hipLaunchKernelGGL((gemm_kernel<128, TA, TB, 2>), grid, dim3(GT), 0, st, g);
 }
 
 }  // namespace
