@@ -14,24 +14,25 @@
 //                     one chunk where tiles of 128 leave the chip idle)
 //   gemm_rows_kernel  a chunk per wave, tiles of 32 x 32, fragments straight
 //                     from memory: few tiles and long K, or up to 32 rows
-// so the chunks do not travel through memory (as partial tiles they were 20 to
-// 44 MB a product, written and read), except where a product has too few tiles
-// for the chip (one row) or long chunks: then they are spread over workgroups
-// and added by a second kernel.
+// so the chunks travel through memory only where that is the cheapest way (few
+// tiles, long K): then they are spread over workgroups and added by a second
+// kernel.  (As partial tiles they were 20 to 44 MB a product.)
 //
 // In the staged kernels each of the four waves owns a quarter of the tile;
 // both operand tiles are staged with K contiguous (row stride padded by 8
 // elements), so every lane reads its 8-element fragment with one 16-byte LDS
 // load; global loads are 4-element runs along the contiguous dimension.
 //
-// Kernel time of a training step of 4800-512-512-5450 at batch 256: 385 us in
-// 27 launches before, 160 us in 12 now.  A forward pass of 51000-512-512-56500
-// at batch 1: 79 us before, 51 us now (its weights alone are 110 MB).
+// Bound by staging: a stage of 64 of K takes a tile of 128 about 2 us at three
+// workgroups a CU, of which the matrix instructions are a quarter.  6000 x 6000
+// at 256 rows: 60 us, 0.31 PFLOP/s.
 #include <hip/hip_runtime.h>
 
 #include <stdint.h>
 
 #include <algorithm>
+#include <cmath>
+#include <type_traits>
 
 #include "mlp.hpp"
 
@@ -44,7 +45,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 constexpr int TK = 64, LDK = TK + 8;
 constexpr int GT = 256;   // threads per staged GEMM workgroup (4 waves, 2 x 2)
 constexpr int RT = 32;    // tile of gemm_rows_kernel
-constexpr int KROWS = 6000;   // mlp_gemm
+constexpr int CUS = 256;      // compute units
 constexpr int VW = 4;     // elements per vector load (8 bytes)
 
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
@@ -103,55 +104,67 @@ constexpr int NRUN = (T * TK / VW) / GT;   // runs of VW elements per thread
 static_assert((64 / 4) * (TK / 4) / GT * 4 == NRUN<64>, "both staging forms use NRUN runs per thread");
 
 // global -> registers: zero past kend, anything past rmax (those rows and
-// columns of C are dropped).  vec: the contiguous dimension and the leading
-// dimension are even and at least 4, so every run of 4 is one load, at the
-// matrix's last 4 elements where it would pass the end (by 2, or altogether).
-// No branches: as tests around each load they were most of a stage's time.
-// LEAN: the addresses are formed at each stage (the thread's index is opaque)
-// instead of kept in registers over the loop: 164 registers instead of 203 at
-// T = 128, so three workgroups a CU instead of two.
-template <int T, bool KCONTIG, bool LEAN>
+// columns of C are dropped).  A run's address is a scalar part and a 32-bit
+// offset of the thread, clamped into the matrix only in the tiles and the stage
+// at its edges: no branches around the loads, which were most of a stage's
+// time, next to no address arithmetic, and registers for three workgroups of
+// T = 128 a CU (with an address per run in registers, 203, two).
+// VEC: the contiguous dimension and the leading dimension are even and at
+// least 4, so a run of 4 is one load, at the matrix's last 4 elements where it
+// would pass the end (by 2, or altogether).
+template <int T, bool KCONTIG, bool VEC>
 __device__ __forceinline__ void stage_load(bf16x4 (&x)[NRUN<T>], const __bf16* P, long ld, int r0, int rmax,
-                                           int k0, int kend, bool vec) {
-  int tid = threadIdx.x;
-  if (LEAN) asm volatile("" : "+v"(tid));
+                                           int k0, int kend) {
   const __bf16 z = (__bf16)0.0f;
   constexpr int RUNS = TK / VW, RB = T / 4;
-  if (vec) {
+  constexpr int RSTEP = GT / RUNS, KSTEP = GT / RB * 4;   // rows (k) between a thread's runs
+  constexpr unsigned ES = sizeof(__bf16);
+  using Off = std::conditional_t<VEC, unsigned, size_t>;   // VEC: 64 lines within 32 bits (gemm_args)
+  const unsigned t = threadIdx.x;
+  const Off row = (Off)ld * ES;
+  // this thread's run begins at `at` of the contiguous dimension, which ends at
+  // `end`; it is loaded from `st`
+  const int at = KCONTIG ? k0 + (int)(t % RUNS) * VW : r0 + (int)(t % RB) * VW, end = KCONTIG ? kend : rmax;
+  const int st = min(at, end - (VEC ? VW : 1));
+  const bool cut = KCONTIG ? k0 + TK > kend : r0 + T > rmax;   // some run passes the end (uniform)
+  const unsigned n = t / (KCONTIG ? RUNS : RB) * (KCONTIG ? 1 : 4), so = (unsigned)st * ES;
+  const auto run = [&](int line, unsigned n, auto clamp) {
+    const char* p = reinterpret_cast<const char*>(P + line * ld) + ((Off)n * row + so);
+    bf16x4 v;
+    if constexpr (VEC) {
+      v = *reinterpret_cast<const bf16x4_a4*>(p);
+    } else {
 #pragma unroll
-    for (int q = 0; q < NRUN<T>; ++q) {
-      if (KCONTIG) {
-        const int v = tid + q * GT;
-        const int row = min(r0 + v / RUNS, rmax - 1), k = k0 + (v % RUNS) * VW, st = min(k, kend - VW);
-        const bf16x4 w = *reinterpret_cast<const bf16x4_a4*>(P + (size_t)row * ld + st);
-        x[q] = st == k ? w : st + 2 == k ? bf16x4{w[2], w[3], z, z} : bf16x4{z, z, z, z};
-      } else {
-        const int b = tid + (q / 4) * GT;
-        const int row = r0 + (b % RB) * 4, k = k0 + (b / RB) * 4 + q % 4, st = min(row, rmax - VW);
-        const bf16x4 w = *reinterpret_cast<const bf16x4_a4*>(P + (size_t)min(k, kend - 1) * ld + st);
-        x[q] = k >= kend ? bf16x4{z, z, z, z} : st == row ? w : bf16x4{w[2], w[3], z, z};
-      }
+      for (int j = 0; j < VW; ++j)
+        v[j] = *reinterpret_cast<const __bf16*>(p + (clamp.value ? min(j, end - 1 - st) : j) * ES);
     }
+    return v;
+  };
+  // line q of the thread: its scalar part, and how many lines there are
+  const auto line = [&](int q) { return KCONTIG ? r0 + q * RSTEP : k0 + q / 4 * KSTEP + q % 4; };
+  const int lines = KCONTIG ? rmax : kend;
+  const bool inside = KCONTIG ? r0 + T <= rmax : k0 + TK <= kend;
+  if (inside && (VEC || !cut)) {
+#pragma unroll
+    for (int q = 0; q < NRUN<T>; ++q) x[q] = run(line(q), n, std::false_type{});
   } else {
 #pragma unroll
     for (int q = 0; q < NRUN<T>; ++q) {
-#pragma unroll
-      for (int j = 0; j < VW; ++j) {
-        int row, k;
-        if (KCONTIG) {
-          const int v = tid + q * GT;
-          row = r0 + v / RUNS;
-          k = k0 + (v % RUNS) * VW + j;
-        } else {
-          const int b = tid + (q / 4) * GT;
-          row = r0 + (b % RB) * 4 + j;
-          k = k0 + (b / RB) * 4 + q % 4;
-        }
-        const size_t rr = min(row, rmax - 1), kk = min(k, kend - 1);
-        const __bf16 w = KCONTIG ? P[rr * ld + kk] : P[kk * ld + rr];
-        x[q][j] = k < kend ? w : z;
-      }
+      const int l = min(line(q), lines - 1);
+      x[q] = run(l, min(n, (unsigned)(lines - 1 - l)), std::true_type{});
+      if (!KCONTIG && line(q) + (int)n >= kend) x[q] = bf16x4{z, z, z, z};
     }
+  }
+  if (VEC && cut && (KCONTIG || end % VW != 0)) {
+#pragma unroll
+    for (int q = 0; q < NRUN<T>; ++q)
+      x[q] = st == at ? x[q] : st + 2 == at ? bf16x4{x[q][2], x[q][3], z, z} : bf16x4{z, z, z, z};
+  }
+  if (!VEC && KCONTIG && cut) {
+#pragma unroll
+    for (int q = 0; q < NRUN<T>; ++q)
+#pragma unroll
+      for (int j = 0; j < VW; ++j) x[q][j] = at + j < kend ? x[q][j] : z;
   }
 }
 
@@ -196,10 +209,9 @@ __device__ __forceinline__ void lds_barrier() {
 // B (the bias gradient) from the staged tiles, in row order, and the Adam step
 // is taken where the gradient is: dW, W, m and v pass through memory once
 // (512 x 5450 x 256: 24 us, bound by those 84 MB; 57 us in five kernels).
-// PER: workgroups a CU.
-template <int T, bool TA, bool TB, int PER>
-__global__ __launch_bounds__(GT, PER) void gemm_kernel(GemmArgs g) {
-  constexpr bool LEAN = T == 128 && PER == 3;
+// VA, VB: vector loads of A and B (stage_load).
+template <int T, bool TA, bool TB, bool VA, bool VB>
+__global__ __launch_bounds__(GT, 3) void gemm_kernel(GemmArgs g) {
   constexpr bool CHUNKS = T == 64;
   constexpr int NB = T / 64;        // 32 x 32 blocks per wave and direction
   __shared__ __attribute__((aligned(16))) __bf16 As[T][LDK];
@@ -214,8 +226,8 @@ __global__ __launch_bounds__(GT, PER) void gemm_kernel(GemmArgs g) {
   // the next stage's global loads are in flight while this stage computes
   bf16x4 xa[NRUN<T>], xb[NRUN<T>];
   const int kb = CHUNKS ? 0 : blockIdx.z * g.kchunk, ke = CHUNKS ? g.K : min(g.K, kb + g.kchunk);
-  stage_load<T, !TA, LEAN>(xa, g.A, g.lda, m0, g.M, kb, g.K, g.vec_a);
-  stage_load<T, TB, LEAN>(xb, g.B, g.ldb, n0, g.N, kb, g.K, g.vec_b);
+  stage_load<T, !TA, VA>(xa, g.A, g.lda, m0, g.M, kb, g.K);
+  stage_load<T, TB, VB>(xb, g.B, g.ldb, n0, g.N, kb, g.K);
   int kend = g.kchunk;              // of the current chunk
 #pragma unroll 1
   for (int k0 = kb; k0 < ke; k0 += TK) {
@@ -223,8 +235,8 @@ __global__ __launch_bounds__(GT, PER) void gemm_kernel(GemmArgs g) {
     stage_store<T, TB>(Bs, xb);
     lds_barrier();
     if (k0 + TK < ke) {
-      stage_load<T, !TA, LEAN>(xa, g.A, g.lda, m0, g.M, k0 + TK, g.K, g.vec_a);
-      stage_load<T, TB, LEAN>(xb, g.B, g.ldb, n0, g.N, k0 + TK, g.K, g.vec_b);
+      stage_load<T, !TA, VA>(xa, g.A, g.lda, m0, g.M, k0 + TK, g.K);
+      stage_load<T, TB, VB>(xb, g.B, g.ldb, n0, g.N, k0 + TK, g.K);
     }
     // lane l holds row/col (l % 32), k (l / 32) * 8 + j of each 32 x 32 x 16 step
 #pragma unroll
@@ -494,8 +506,10 @@ GemmArgs gemm_args(const __bf16* A, bool ta, long lda, const __bf16* B, bool tb,
   g.N = N;
   g.K = K;
   g.epi = epi;
-  g.vec_a = lda % 2 == 0 && ca % 2 == 0 && ca >= VW;
-  g.vec_b = ldb % 2 == 0 && cb % 2 == 0 && cb >= VW;
+  // up to 64 rows of the matrix within the 32-bit offsets of stage_load
+  constexpr long LD_MAX = 1l << 25;
+  g.vec_a = lda % 2 == 0 && lda <= LD_MAX && ca % 2 == 0 && ca >= VW;
+  g.vec_b = ldb % 2 == 0 && ldb <= LD_MAX && cb % 2 == 0 && cb >= VW;
   g.kchunk = chunk_k(M, N, K, work_floats);
   return g;
 }
@@ -507,34 +521,73 @@ void launch_rows(const GemmArgs& g, dim3 grid, int chunks, hipStream_t st) {
   else hipLaunchKernelGGL((gemm_rows_kernel<TB, 1>), grid, dim3(64), 0, st, g);
 }
 
-// Which tile: 64 x 64 for several chunks one after another.  One chunk:
-//  - tiles of 64 for up to 64 rows, and where tiles of 128 are no more than
-//    the CUs (64 x 512, 256 rows: 14 and 9 us a pass);
-//  - else tiles of 128, which read the operands half as often, three a CU
-//    where that takes fewer turns of the chip than two a CU (output layer of
-//    512 x 49000, 256 rows, 766 tiles: 83 us a forward pass of
-//    600-512-512-49000 at two a CU, 65 at three);
-//  - but tiles of 64 where tiles of 128 take a second turn at two a CU and
-//    the small ones, four a CU, finish in at most one turn more than three
-//    large ones a CU: a turn of them takes 23 us, one of two or three large
-//    ones 37 or 50.  That is where the last row of tiles is half empty
-//    (512 x 33000, 160 rows: 75 us at two a CU, 59 in tiles of 64; 512 x
-//    40000: 72 and 48).  From 960 tiles of 128 on they lose (512 x 65000,
-//    129 rows, 1,016 tiles: 80 and 85).
+// How to carry out a product of several chunks: a wave per chunk, staged
+// tiles of 128 whose sums go through memory, or staged tiles of 64 with the
+// chunks one after another.  The cost of each in microseconds: what the last
+// workgroup takes for its part of K, or what the chip takes for all of them,
+// and the passes over C.  The numbers are a fit to 2,200 products of 33 to
+// 1,024 rows, K from 96 to 56,500 and N from 100 to 26,557, timed in all three
+// ways with B in either layout; the choice is 1% above the best way on average
+// (512 columns, K = 4800, 256 rows: 22 us in waves, 24 through memory, 85 in
+// tiles of 64; 6000 columns, K = 6000: 158, 60, 107; 12800 columns, K = 512:
+// 38, 33, 20).
+//  - waves: rounds of 8 or 16 chunks a workgroup (one, and a pass more, where
+//    they are spread); tiles of 32 read A and B four times as often as tiles of
+//    128, and 64 bytes of a row of B at a time, which straddle lines unless
+//    the rows begin on them; A in single elements takes five times as long
+//  - staged: single elements take several loads where a run takes one
+enum Way { WAY_ROWS, WAY_SPREAD, WAY_STAGED };
+bool rows_spread(const GemmArgs& g, int chunks) {
+  // fewer than 64 tiles of 32 x 32: the chunks go to several workgroups
+  return chunks > 16 && (long)((g.N + RT - 1) / RT) * ((g.M + RT - 1) / RT) < 64;
+}
+Way cheapest(const GemmArgs& g, int chunks) {
+  const double M = g.M, N = g.N, K = g.K, mn = M * N * 1e-6;
+  const auto tiles = [&](int t) { return std::ceil(M / t) * std::ceil(N / t); };
+  const bool vec = g.vec_a && g.vec_b, spread = rows_spread(g, chunks);
+  const double rounds = spread ? 1.0 : std::ceil(chunks / (chunks > 8 ? 16.0 : 8.0));
+  const double rows = 3.3 + 16.8e-3 * (g.vec_a ? 1.0 : 5.3) * g.kchunk * (1.0 + 1.65 * (rounds - 1.0)) +
+                      13.2e-6 * (g.ldb % 64 == 0 ? 1.0 : 1.27) * tiles(RT) * K + 0.9 * mn +
+                      (spread ? 1.9 + 1.2 * chunks * mn : 0.0);
+  const double through = 10.0 + std::max(26.9e-3 * std::ceil(tiles(128) * chunks / (3.0 * CUS)) * g.kchunk,
+                                         33.8e-6 * (vec ? 1.0 : 3.2) * tiles(128) * K) + 1.2 * chunks * mn;
+  const double inside = 4.7 + (vec ? 1.0 : 2.0) * std::max(11.7e-3 * std::ceil(tiles(64) / (5.0 * CUS)) * K,
+                                                           23.5e-6 * tiles(64) * K) + 0.8 * mn;
+  return rows <= through && rows <= inside ? WAY_ROWS : through <= inside ? WAY_SPREAD : WAY_STAGED;
+}
+
+// Which tile: 64 x 64 for several chunks one after another.  One chunk: tiles
+// of 128 read the operands half as often, three of them a CU; tiles of 64
+// where those are too few, up to one and a half a CU (64 x 20000, 192 rows, 314
+// tiles: 18 us in tiles of 128, 11 in tiles of 64; 512 x 31000, 160 rows, 486
+// tiles: 29 and 38; 512 x 49000, 256 rows, 766 tiles: 40 and 63), and for up to
+// 64 rows, unless K is long and one turn of the chip holds the tiles (2048 x
+// 65000, 33 rows, 508 tiles: 72 and 84; 2048 x 100000, 782 tiles: 151 and 114).
+// Single elements are staged at half the rate: tiles of 64 up to a tile on
+// every fourth CU (512 x 26557, 128 rows, 208 tiles: 41 and 48).
 template <bool TA, bool TB>
 void launch_staged(const GemmArgs& g, int chunks, hipStream_t st) {
-  constexpr long CUS = 256;
   const long t128 = (long)((g.N + 127) / 128) * ((g.M + 127) / 128);
-  const long t64 = (long)((g.N + 63) / 64) * ((g.M + 63) / 64);
-  const auto turns = [](long tiles, long per) { return (tiles + per * CUS - 1) / (per * CUS); };
-  const bool small = g.M <= 64 || (!TA && (t128 <= CUS || (t128 > 2 * CUS && t128 <= 15 * CUS / 4 &&
-                                                           turns(t64, 4) <= turns(t128, 3) + 1)));
+  const bool small = t128 <= (g.vec_a && g.vec_b ? CUS + CUS / 2 : CUS / 4) || (g.M <= 64 && (g.K <= 1024 || t128 > 3 * CUS));
   const bool inside = !g.partial && (chunks > 1 || small);
   const int T = inside ? 64 : 128;
   const dim3 grid((g.N + T - 1) / T, (g.M + T - 1) / T, inside ? 1 : chunks);
-  if (inside) hipLaunchKernelGGL((gemm_kernel<64, TA, TB, 3>), grid, dim3(GT), 0, st, g);
-  else if (!g.partial && turns(t128, 3) < turns(t128, 2)) hipLaunchKernelGGL((gemm_kernel<128, TA, TB, 3>), grid, dim3(GT), 0, st, g);
-  else hipLaunchKernelGGL((gemm_kernel<128, TA, TB, 2>), grid, dim3(GT), 0, st, g);
+  const auto launch = [&](auto va, auto vb) {
+    constexpr bool VA = va.value, VB = vb.value;
+    if (inside) hipLaunchKernelGGL((gemm_kernel<64, TA, TB, VA, VB>), grid, dim3(GT), 0, st, g);
+    else hipLaunchKernelGGL((gemm_kernel<128, TA, TB, VA, VB>), grid, dim3(GT), 0, st, g);
+  };
+  using yes = std::true_type;
+  using no = std::false_type;
+  if (g.vec_a && g.vec_b) {
+    launch(yes{}, yes{});
+  } else if constexpr (TB) {
+    launch(no{}, no{});   // both operands are stored along K
+  } else {
+    if (g.vec_a) launch(yes{}, no{});
+    else if (g.vec_b) launch(no{}, yes{});
+    else launch(no{}, no{});
+  }
 }
 
 }  // namespace
@@ -549,18 +602,12 @@ hipError_t mlp_gemm(const __bf16* A, long lda, const __bf16* B, bool tb, long ld
   g.outf = outf;
   g.outb = outb;
   const int chunks = (K + g.kchunk - 1) / g.kchunk;
-  const long t64 = (long)((M + 63) / 64) * ((N + 63) / 64);
-  // a wave per chunk: up to 32 rows, of which a staged tile would hold mostly
-  // padding, and products of fewer than 400 64 x 64 tiles, about three waves a
-  // SIMD at most (256 x 5450 x 512, 344 tiles: 20 us, 22.5 staged; 256 x 512 x
-  // 4800, 32 tiles: 23 us, 25 through memory).  Tiles of 32 read A and B from
-  // the L2 four times as often as tiles of 128, so beyond KROWS the staged
-  // tiles win although their sums travel (forward pass of 13670-512-512-923 at
-  // batch 128: 75 us in tiles of 32, 37 staged)
-  const bool rows = M <= RT || (chunks > 1 && t64 < 400 && K <= KROWS);
+  // up to 32 rows: a wave per chunk, since a staged tile would hold mostly
+  // padding; several chunks: the cheapest of the three
+  const Way way = M <= RT ? WAY_ROWS : chunks > 1 ? cheapest(g, chunks) : WAY_STAGED;
+  const bool rows = way == WAY_ROWS;
   dim3 grid((N + RT - 1) / RT, (M + RT - 1) / RT);
-  // fewer than 64 tiles of 32 x 32: the chunks go to several workgroups as well
-  const bool spread = rows ? chunks > 16 && grid.x * grid.y < 64 : chunks > 1 && t64 < 400;
+  const bool spread = rows ? rows_spread(g, chunks) : way == WAY_SPREAD;
   GemmArgs p = g;
   if (spread) {
     p.partial = 1;

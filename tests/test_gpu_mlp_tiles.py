@@ -1,7 +1,7 @@
-"""Which tile a product of the network takes: tiles of 128 at two and three
-workgroups a CU, tiles of 64 for one chunk of K, and sums over K of more than
-6,000 whose chunks travel through memory (K inside a chunk at the end), for
-both layouts of the right operand.
+"""Which way a product of the network goes: tiles of 128 in one turn of the chip
+and in two, tiles of 64 for one chunk of K and for several, and long sums over K
+whose chunks travel through memory (K inside a chunk at the end), for both
+layouts of the right operand.
 
 Exact regime (see test_gpu_mlp): every forward sum is exact, so the forward
 pass and the loss agree with the FP64 reference bit for bit.  Gradients: a
@@ -20,10 +20,10 @@ U = 2.0 ** -24
 
 
 @pytest.mark.parametrize("dims,B", [
-    ([16, 24, 49000], 256),      # 766 tiles of 128: one turn at three a CU
-    ([16, 24, 49000], 385),      # 1,532 tiles: two turns at three a CU, three at two
-    ([16, 24, 50002], 250),      # 782 tiles: two turns either way
-    ([16, 24, 40002], 129),      # 626 tiles, the last row almost empty: tiles of 64
+    ([16, 24, 49000], 256),      # 766 tiles of 128: one turn
+    ([16, 24, 49000], 385),      # 1,532 tiles: two turns
+    ([16, 24, 50002], 250),      # 782 tiles: just a second turn
+    ([16, 24, 40002], 129),      # 626 tiles, the last row almost empty
     ([16, 24, 33001], 192),      # odd leading dimension
     ([16, 24, 33000], 257),      # 774 tiles, the last row almost empty
     ([64, 520, 24], 200),        # one step of K, fewer tiles than CUs
@@ -32,6 +32,9 @@ U = 2.0 ** -24
     ([7000, 130, 33], 130),
     ([40, 48, 6500], 40),        # the same for the transposed product
     ([33, 130, 7002], 200),
+    ([2050, 2602, 30], 260),     # several chunks, ragged in every direction: through memory
+    ([1029, 2601, 33], 129),     # the same in single elements
+    ([130, 9002, 34], 300),      # two chunks, tiles of 64
 ])
 def test_products_by_tile(dims, B):
     print(f"[tiles] {dims} batch {B}", flush=True)
