@@ -94,22 +94,24 @@ __device__ __forceinline__ bool allreduce(const GridTeam& T, LdsT& L, int ns, Sl
     const int s = slot_of(q);
     const unsigned long long* in = T.C.in + (size_t)s * G * 2;
     double sum = 0.0;
-    for (int w0 = lane; w0 < G; w0 += 256) {
+    for (int w0 = 0; w0 < G && ok; w0 += 256) {
       double v[4] = {0.0, 0.0, 0.0, 0.0};
-      while (ok) {
+      while (true) {
         bool all = true;
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
-          if (w0 + 64 * t < G) all = get_pair(in + (size_t)(w0 + 64 * t) * 2, ep, v[t]) && all;
-        if (all) break;
-        if (wall_clock64() - t0 > T.limit) ok = false;
+        for (int t = 0; t < 4; ++t) {
+          const int w = w0 + 64 * t + lane;
+          if (w < G) all = get_pair(in + (size_t)w * 2, ep, v[t]) && all;
+        }
+        if (__all(all)) break;
+        if (wall_clock64() - t0 > T.limit) {
+          ok = false;
+          break;
+        }
       }
       sum += (v[0] + v[1]) + (v[2] + v[3]);
     }
-    if (!__all(ok)) {   // of the lanes of this wave
-      ok = false;
-      break;
-    }
+    if (!ok) break;
     sum = wave_sum(sum);
     if (lane < COMM_COPIES) put_pair(T.C.out + ((size_t)lane * SL_COUNT + s) * 2, sum, ep);
   }
