@@ -136,6 +136,7 @@ struct Batch {
   std::vector<InstDesc> desc;
   InstDesc* d_desc = nullptr;
   int* d_queue = nullptr;
+  unsigned long long* d_deadline = nullptr;
   int* d_order = nullptr;
   Ctl* d_ctl = nullptr;
   long* d_offx = nullptr;
@@ -1195,9 +1196,16 @@ BatchArgs batch_args(Handle* h, long long stop_at) {
   a.queue = B->d_queue;
   a.S = h->ds;
   a.stop_at = stop_at;
-  const double lim = h->s.time_limit;
-  a.limit_ticks = (lim > 0 && lim < 1e9) ? (unsigned long long)(lim * 1e3 * h->rate_khz) : 0ull;
+  a.deadline = B->d_deadline;
   return a;
+}
+
+// queues, iterates and the deadline before a launch of the batch
+hipError_t reset_batch(Handle* h, hipStream_t st) {
+  Batch* B = h->B;
+  const double lim = h->s.time_limit;
+  const unsigned long long ticks = (lim > 0 && lim < 1e9) ? (unsigned long long)(lim * 1e3 * h->rate_khz) : 0ull;
+  return launch_batch_reset(B->d_desc, B->count, B->d_queue, B->d_deadline, ticks, st);
 }
 
 // the instances of the register-resident core, then the others, each with a
@@ -1268,6 +1276,7 @@ int setup_batch(Handle* h) {
   B->d_ctl = B->mem.alloc<Ctl>(count);
   B->d_desc = B->mem.alloc<InstDesc>(count);
   B->d_queue = B->mem.alloc<int>(2);
+  B->d_deadline = B->mem.alloc<unsigned long long>(1);
   B->d_norm = B->mem.alloc<double>(count);
   B->offx.assign(count + 1, 0);
   B->offy.assign(count + 1, 0);
@@ -1353,7 +1362,7 @@ int setup_batch(Handle* h) {
           set_lanes(h, da, dat);
           rc = upload_desc(h, st);
           if (rc != PDHCG_OK) return rc;
-          HIPCHK(launch_batch_reset(B->d_desc, count, B->d_queue, st));
+          HIPCHK(reset_batch(h, st));
           HIPCHK(hipEventRecord(e0, st));
           HIPCHK(launch_batches(h, it, nullptr, st));
           HIPCHK(hipEventRecord(e1, st));
@@ -1389,7 +1398,7 @@ int capture_batch(Handle* h) {
   if (B->exec) return PDHCG_OK;
   if (!B->cap) HIPCHK(hipStreamCreateWithFlags(&B->cap, hipStreamNonBlocking));
   HIPCHK(hipStreamBeginCapture(B->cap, hipStreamCaptureModeThreadLocal));
-  hipError_t e = launch_batch_reset(B->d_desc, B->count, B->d_queue, B->cap);
+  hipError_t e = reset_batch(h, B->cap);
   if (e == hipSuccess) e = launch_batches(h, h->s.max_iter, nullptr, B->cap);
   if (e == hipSuccess)
     e = launch_batch_gather(B->d_desc, B->count, B->d_offx, B->d_offy, B->d_outx, B->d_outy,
@@ -1810,7 +1819,7 @@ int pdhcg_solve_batch(pdhcg_handle* h, const double* const* x0s, const double* c
     dpt = tbuf.alloc<unsigned long long>((size_t)PT_COUNT * pgrid);
     if (tbuf.err != hipSuccess) return PDHCG_E_MEM;
     HIPCHK(hipMemsetAsync(dpt, 0, sizeof(unsigned long long) * PT_COUNT * pgrid, st));
-    HIPCHK(launch_batch_reset(B->d_desc, B->count, B->d_queue, st));
+    HIPCHK(reset_batch(h, st));
     HIPCHK(launch_batches(h, h->s.max_iter, dpt, st));
     HIPCHK(launch_batch_gather(B->d_desc, B->count, B->d_offx, B->d_offy, B->d_outx, B->d_outy,
                                h->s.scheme == PDHCG_SCHEME_AVG ? 1 : 0, st));

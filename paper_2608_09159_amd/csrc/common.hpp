@@ -236,7 +236,7 @@ struct BatchArgs {
   int* queue;              // positions taken (reset to 0 before a launch)
   DevSettings S;
   long long stop_at;       // per-instance iteration cap of this launch
-  unsigned long long limit_ticks;   // per-launch wall-clock budget (0 = none)
+  const unsigned long long* deadline;   // wall-clock tick of the whole batch, set at its reset (0: none)
   unsigned long long* ptimes;       // [grid][PT_COUNT] phase timers, nullable
 };
 

@@ -1799,10 +1799,12 @@ __global__ __launch_bounds__(BLOCK) void dual_slack_kernel(DevProblem P, const d
 // batch kernels: independent instances, one workgroup per instance at a time
 // ---------------------------------------------------------------------------
 // before every batch launch: control blocks zeroed, scaled warm starts (or
-// zeros) into zb and y, root warm starts unset (NaN), both queues at 0
-__global__ __launch_bounds__(BLOCK) void batch_reset_kernel(const InstDesc* desc, int count,
-                                                           int* queue) {
+// zeros) into zb and y, root warm starts unset (NaN), both queues at 0, and the
+// deadline of all that follows (limit: ticks from now, 0 for none)
+__global__ __launch_bounds__(BLOCK) void batch_reset_kernel(const InstDesc* desc, int count, int* queue,
+                                                           unsigned long long* deadline, unsigned long long limit) {
   if (blockIdx.x == 0 && threadIdx.x < 2) queue[threadIdx.x] = 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) *deadline = limit ? wall_clock64() + limit : 0ull;
   for (int i = blockIdx.x; i < count; i += gridDim.x) {
     const InstDesc& D = desc[i];
     const long n = D.P.n, m = D.P.m;
@@ -1820,7 +1822,7 @@ __global__ __launch_bounds__(BLOCK) void batch_reset_kernel(const InstDesc* desc
 template <class LdsT, class Core>
 __device__ __forceinline__ void batch_body(const BatchArgs& B, LdsT& L, Core core) {
   __shared__ int slot;
-  const unsigned long long deadline = B.limit_ticks ? wall_clock64() + B.limit_ticks : 0ull;
+  const unsigned long long deadline = *B.deadline;
   const bool prof = B.ptimes != nullptr;
   if (threadIdx.x < PT_COUNT) L.pt[threadIdx.x] = 0ull;
   for (;;) {
@@ -2243,9 +2245,10 @@ hipError_t launch_batch(const BatchArgs& args, bool res, bool cones, bool ext, i
   return e != hipSuccess ? e : hipLaunchKernel(k, dim3(grid), dim3(BLOCK), params, (size_t)lds_bytes, st);
 }
 
-hipError_t launch_batch_reset(const InstDesc* desc, int count, int* queue, hipStream_t st) {
+hipError_t launch_batch_reset(const InstDesc* desc, int count, int* queue, unsigned long long* deadline,
+                              unsigned long long limit, hipStream_t st) {
   const int grid = std::max(1, std::min(count, 4096));
-  hipLaunchKernelGGL(batch_reset_kernel, dim3(grid), dim3(BLOCK), 0, st, desc, count, queue);
+  hipLaunchKernelGGL(batch_reset_kernel, dim3(grid), dim3(BLOCK), 0, st, desc, count, queue, deadline, limit);
   return hipGetLastError();
 }
 

@@ -46,7 +46,8 @@ hipError_t launch_project(int type, int dim, long count, const double* alpha, co
 int batch_grid_limit(bool res, bool cones, bool ext, int lds_bytes);
 hipError_t launch_batch(const BatchArgs& args, bool res, bool cones, bool ext, int lds_bytes, int grid,
                         hipStream_t st);
-hipError_t launch_batch_reset(const InstDesc* desc, int count, int* queue, hipStream_t st);
+hipError_t launch_batch_reset(const InstDesc* desc, int count, int* queue, unsigned long long* deadline,
+                              unsigned long long limit, hipStream_t st);
 hipError_t launch_batch_power(const InstDesc* desc, int count, int iters, double* out, hipStream_t st);
 hipError_t launch_batch_gather(const InstDesc* desc, int count, const long* offx, const long* offy,
                                double* ox, double* oy, int avg, hipStream_t st);
