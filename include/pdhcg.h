@@ -321,13 +321,14 @@ int pdhcg_setup(const pdhcg_problem* probs, int32_t count,
  * PDHCG_E_HIP when a device call fails (status is then unset).             */
 int pdhcg_solve(pdhcg_handle* h, const double* x0, const double* y0, pdhcg_result* res);
 
-/* Solve every problem of a batch handle (count > 1 at setup) in one
- * persistent launch, replayed from a HIP graph: each workgroup takes the next
- * instance from a device queue (largest first) and runs the whole restarted
- * PDHG method on it with that instance's own step sizes, primal weight,
- * restarts and inner tolerance, then takes the next.  Every instance runs to
+/* Solve every problem of a batch handle (count > 1 at setup) in one launch of
+ * a HIP graph: each workgroup takes the next instance from a device queue
+ * (largest first) and runs the whole restarted PDHG method on it with that
+ * instance's own step sizes, primal weight, restarts and inner tolerance, then
+ * takes the next.  Instances of up to 512 coordinates and rows have a queue and
+ * a kernel of their own, which runs beside the others'.  Every instance runs to
  * its own termination (tol, max_iter); settings.time_limit bounds the whole
- * launch (instances still running then report PDHCG_TIME_LIMIT).
+ * batch (instances still running then report PDHCG_TIME_LIMIT).
  * x0s/y0s: NULL or host arrays of `count` pointers (each may be NULL;
  * original space; each pointing to memory_kind memory).  res: array of `count` results; their x/y/s pointers may be set.
  * kernel_s of res[0] holds the device time of the launch; setup_s and

@@ -157,7 +157,8 @@ struct Batch {
   bool ext = false;               // some other instance has row bounds, boxes or EXP1 blocks
   int div_a = 2, div_at = 2;      // lanes-per-row rule: lanes <= mean nnz / div
   double tune_s = 0.0;
-  hipStream_t cap = nullptr;      // private stream used for graph capture
+  hipStream_t cap = nullptr, side = nullptr;    // private streams used for graph capture
+  hipEvent_t fork = nullptr, join = nullptr;    // between them
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
 };
@@ -247,8 +248,12 @@ bool sparse_q(const HostInstance& H) { return H.P.rows > 0 && !H.p_diag && !H.q_
 // (512 of each): the LDS it needs and whether the columns of R fit in it too.
 // Four coordinates a thread do not fit the 256 registers beside the vectors
 // (1,000 portfolios of 50 to 2,000 assets: 25 ms, 22 ms in the general core).
-// The rule looks at the instance alone, so an instance solved alone and in a
-// batch takes the same core.
+// (Batches of them alone, calls with 48 iterations: 64 portfolios of 50 to 440
+// assets 3.5 ms in the general core, 2.0 here; 512 of them 7.2 and 6.0; 1,000:
+// 13.3 and 10.8; 1,500 tiny QPs 114 and 72.)
+// The rule looks at the instance alone, so an instance takes the same core in a
+// batch and alone on one workgroup (grid_dim 1; by itself a single solve of more
+// than 341 coordinates or rows takes a grid).
 int res_one(const Handle* h, const HostInstance& H, DevProblem& P) {
   P.res = RES_NONE;
   const long bs = block_size();
@@ -1208,22 +1213,36 @@ hipError_t reset_batch(Handle* h, hipStream_t st) {
   return launch_batch_reset(B->d_desc, B->count, B->d_queue, B->d_deadline, ticks, st);
 }
 
-// the instances of the register-resident core, then the others, each with a
-// queue of its own
-hipError_t launch_batches(Handle* h, long long stop_at, unsigned long long* ptimes, hipStream_t st) {
+// The instances of the register-resident core and the others, each kind by a
+// kernel with a queue of its own.  The others are larger and start first; with
+// `side` the two kernels run side by side, so that the small instances take the
+// places that the large ones leave, and the batch ends with its slowest
+// instance.  (Calls with 400 and 1,000 portfolios of 50 to 2,000 assets: 15.4
+// and 21.6 ms with the kernels one after the other, small ones first, 13.3 and
+// 20.9 side by side; 12.9 and 21.9 in the general core's one queue.)
+hipError_t launch_batches(Handle* h, long long stop_at, unsigned long long* ptimes, hipStream_t st, hipStream_t side) {
   Batch* B = h->B;
   BatchArgs a = batch_args(h, stop_at);
   a.ptimes = ptimes;
+  const bool both = B->nres > 0 && B->nres < B->count;
   hipError_t e = hipSuccess;
-  if (B->nres > 0) {
-    a.count = B->nres;
-    e = launch_batch(a, true, B->cones_res, false, B->lds_res, B->grid_res, st);
+  if (both && side) {
+    e = hipEventRecord(B->fork, st);
+    if (e == hipSuccess) e = hipStreamWaitEvent(side, B->fork, 0);
   }
   if (e == hipSuccess && B->nres < B->count) {
-    a.first = B->nres;
-    a.count = B->count;
-    a.queue = B->d_queue + 1;
-    e = launch_batch(a, false, B->cones, B->ext, 0, B->grid, st);
+    BatchArgs g = a;
+    g.first = B->nres;
+    g.queue = B->d_queue + 1;
+    e = launch_batch(g, false, B->cones, B->ext, 0, B->grid, st);
+  }
+  if (e == hipSuccess && B->nres > 0) {
+    a.count = B->nres;
+    e = launch_batch(a, true, B->cones_res, false, B->lds_res, B->grid_res, both && side ? side : st);
+  }
+  if (both && side) {
+    if (e == hipSuccess) e = hipEventRecord(B->join, side);
+    if (e == hipSuccess) e = hipStreamWaitEvent(st, B->join, 0);
   }
   return e;
 }
@@ -1364,7 +1383,7 @@ int setup_batch(Handle* h) {
           if (rc != PDHCG_OK) return rc;
           HIPCHK(reset_batch(h, st));
           HIPCHK(hipEventRecord(e0, st));
-          HIPCHK(launch_batches(h, it, nullptr, st));
+          HIPCHK(launch_batches(h, it, nullptr, st, nullptr));
           HIPCHK(hipEventRecord(e1, st));
           HIPCHK(hipEventSynchronize(e1));
           float ms = 0.0f;
@@ -1396,10 +1415,13 @@ int setup_batch(Handle* h) {
 int capture_batch(Handle* h) {
   Batch* B = h->B;
   if (B->exec) return PDHCG_OK;
-  if (!B->cap) HIPCHK(hipStreamCreateWithFlags(&B->cap, hipStreamNonBlocking));
+  for (hipStream_t* q : {&B->cap, &B->side})
+    if (!*q) HIPCHK(hipStreamCreateWithFlags(q, hipStreamNonBlocking));
+  for (hipEvent_t* v : {&B->fork, &B->join})
+    if (!*v) HIPCHK(hipEventCreateWithFlags(v, hipEventDisableTiming));
   HIPCHK(hipStreamBeginCapture(B->cap, hipStreamCaptureModeThreadLocal));
   hipError_t e = reset_batch(h, B->cap);
-  if (e == hipSuccess) e = launch_batches(h, h->s.max_iter, nullptr, B->cap);
+  if (e == hipSuccess) e = launch_batches(h, h->s.max_iter, nullptr, B->cap, B->side);
   if (e == hipSuccess)
     e = launch_batch_gather(B->d_desc, B->count, B->d_offx, B->d_offy, B->d_outx, B->d_outy,
                             h->s.scheme == PDHCG_SCHEME_AVG ? 1 : 0, B->cap);
@@ -1418,7 +1440,10 @@ void free_batch(Batch* B) {
   if (!B) return;
   if (B->exec) (void)hipGraphExecDestroy(B->exec);
   if (B->graph) (void)hipGraphDestroy(B->graph);
-  if (B->cap) (void)hipStreamDestroy(B->cap);
+  for (hipEvent_t v : {B->fork, B->join})
+    if (v) (void)hipEventDestroy(v);
+  for (hipStream_t q : {B->cap, B->side})
+    if (q) (void)hipStreamDestroy(q);
   B->mem.release();
   delete B;
 }
@@ -1820,7 +1845,7 @@ int pdhcg_solve_batch(pdhcg_handle* h, const double* const* x0s, const double* c
     if (tbuf.err != hipSuccess) return PDHCG_E_MEM;
     HIPCHK(hipMemsetAsync(dpt, 0, sizeof(unsigned long long) * PT_COUNT * pgrid, st));
     HIPCHK(reset_batch(h, st));
-    HIPCHK(launch_batches(h, h->s.max_iter, dpt, st));
+    HIPCHK(launch_batches(h, h->s.max_iter, dpt, st, nullptr));
     HIPCHK(launch_batch_gather(B->d_desc, B->count, B->d_offx, B->d_offy, B->d_outx, B->d_outy,
                                h->s.scheme == PDHCG_SCHEME_AVG ? 1 : 0, st));
   } else {
