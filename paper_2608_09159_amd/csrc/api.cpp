@@ -238,6 +238,12 @@ int long_rows(const Csr& M, long a, long b) {
   return k;
 }
 
+// what the long rows of [a, b) cost a product: a wave looks at each of them in
+// every chunk
+long long_work(const Csr& M, long a, long b, long chunk) {
+  return (long)long_rows(M, a, b) * ((M.ptr[b] - M.ptr[a] + chunk - 1) / chunk);
+}
+
 long res_chunk(long nnz) {
   return std::min<long>(RES_CHUNK_MAX, std::max<long>(block_size(), (nnz + block_size() - 1) / block_size() * block_size()));
 }
@@ -264,6 +270,14 @@ int res_one(const Handle* h, const HostInstance& H, DevProblem& P) {
     return 0;
   const long chunk = res_chunk(nz);
   if (res_lds_bytes(H.n, H.m, H.r, false, chunk, true, true) > RES_LDS_DYN) return 0;
+  // long rows: a product takes 0.1 us longer for every eight of them and chunk,
+  // and what an iteration saves grows with the problem (dense A, k x k, 128
+  // iterations here and in the general core: k = 48 1.22 and 1.02 ms, 100 3.2
+  // and 1.7, 192 9.9 and 3.7; 500 columns, 190 rows of 40: 2.6 and 2.1; a row
+  // of 17 at most for each column and 100 rows of 40: 1.4 and 1.7)
+  const long work = long_work(H.A, 0, H.m, chunk) + long_work(H.AT, 0, H.n, chunk) +
+                    (sparse_q(H) ? long_work(H.P, 0, H.n, chunk) : 0);
+  if (10 * work > 520 + 3 * ((long)H.n + H.m)) return 0;
   P.res = RES_ONE;
   P.res_chunk = (int)chunk;
   P.res_r_lds = res_lds_bytes(H.n, H.m, H.r, true, chunk, true, true) <= RES_LDS_DYN ? 1 : 0;
@@ -290,6 +304,13 @@ int res_grid(const HostInstance& H, const std::vector<long>& pc, const std::vect
       return 0;
   }
   const long chunk = res_chunk(nz);
+  // long rows, as on one workgroup; a grid saves more (two workgroups, 380 rows of
+  // 80: 1,000 columns, 1,460 a workgroup, 6.1 ms here and 5.1 in the general core;
+  // 2,000 columns, 760 a workgroup: 4.9 and 5.6)
+  for (int w = 0; w < G; ++w)
+    if (long_work(H.A, pr[w], pr[w + 1], chunk) + long_work(H.AT, pc[w], pc[w + 1], chunk) +
+            (sp ? long_work(H.P, pc[w], pc[w + 1], chunk) : 0) > 1000)
+      return 0;
   size_t lds[2] = {0, 0};
   for (int w = 0; w < G; ++w)
     for (int rl = 0; rl < 2; ++rl)
