@@ -874,11 +874,11 @@ int upload_instance(Handle* h, Instance* I) {
     P.part_lanes = B.upload(lanes);
     if (const char* path = std::getenv("PDHCG_PARTITION_DUMP")) {
       // one line per workgroup: coordinate range, row range, lanes per A^T
-      // row, per A row, SOC group width
+      // row, per A row, SOC group width, register-resident core (RES_*; 0: general)
       if (FILE* f = std::fopen(path, "w")) {
         for (int w = 0; w < G; ++w)
-          std::fprintf(f, "%d %ld %ld %ld %ld %d %d %d\n", w, pc[w], pc[w + 1], pr[w], pr[w + 1], lanes[4 * w],
-                       lanes[4 * w + 1], lanes[4 * w + 2]);
+          std::fprintf(f, "%d %ld %ld %ld %ld %d %d %d %d\n", w, pc[w], pc[w + 1], pr[w], pr[w + 1], lanes[4 * w],
+                       lanes[4 * w + 1], lanes[4 * w + 2], P.res);
         std::fclose(f);
       }
     }
