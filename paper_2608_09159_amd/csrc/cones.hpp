@@ -772,16 +772,23 @@ __device__ __forceinline__ double pow_qroot(double s, double c) {
   return s >= 0.0 ? 0.5 * (s + d) : 2.0 * c / (d - s);
 }
 
+// a^al b^(1-al) >= c for a, b >= 0: by logarithms, each a third of a pow, unless
+// they are within their rounding (|log| ulps) of equality
+__device__ __forceinline__ bool pow_reaches(double a, double b, double al, double c) {
+  const double p = al * log(a), q = (1.0 - al) * log(b), l = log(c), d = p + q - l;
+  if (fabs(d) > 1e-14 * (1.0 + fabs(p) + fabs(q) + fabs(l))) return d > 0.0;
+  return pow(a, al) * pow(b, 1.0 - al) >= c;
+}
+
 __device__ __forceinline__ void project_pow_body(double x, double y, double z, double al, double mx, double my,
                                                  double mz, double out[3], double* warm) {
   if (z == 0.0) { out[0] = fmax(x, 0.0); out[1] = fmax(y, 0.0); out[2] = 0.0; return; }
-  // in the cone, or -M r in its dual: by logarithms, each a third of a pow
-  if (x >= 0.0 && y >= 0.0 && al * log(x) + (1.0 - al) * log(y) >= log(fabs(z))) {
+  if (x >= 0.0 && y >= 0.0 && pow_reaches(x, y, al, fabs(z))) {
     out[0] = x; out[1] = y; out[2] = z; return;
   }
   {
     double p = -mx * x, q = -my * y, w = -mz * z;
-    if (p >= 0.0 && q >= 0.0 && al * log(p / al) + (1.0 - al) * log(q / (1.0 - al)) >= log(fabs(w))) {
+    if (p >= 0.0 && q >= 0.0 && pow_reaches(p / al, q / (1.0 - al), al, fabs(w))) {
       out[0] = out[1] = out[2] = 0.0;
       return;
     }
