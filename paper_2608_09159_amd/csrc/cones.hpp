@@ -118,6 +118,15 @@ __device__ __forceinline__ double rcp_step(double x) {
   return y * (2.0 - x * y);
 }
 
+// a / b from ib = 1 / b: the product, corrected once by its exact remainder.  With ib
+// the quotient 1 / b rounded to nearest this is a / b rounded to nearest (P.
+// Markstein, IBM J. Res. Dev. 34(1), 1990), unless a, b or a / b is near the ends
+// of the exponent range; the product alone is off by up to an ulp and a half.
+__device__ __forceinline__ double quotient(double a, double b, double ib) {
+  const double q = a * ib;
+  return fma(fma(-q, b, a), ib, q);
+}
+
 // A Newton step of size `step` from a point of size `at`, the Newton step
 // before it of size `prev`: small enough, and shrinking fast enough, for the
 // next one to be below the resolution of the point (steps shrink

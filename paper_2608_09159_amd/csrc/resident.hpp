@@ -588,7 +588,7 @@ __device__ __forceinline__ void run_resident(const Run& A, const DevProblem& P, 
     mul_at(t);
     if (qdiag) {
 #pragma unroll
-      for (int j = 0; j < CPT; ++j) if (wave_c(j)) z[j] = (x[j] + tau * t[j] - tau * c[j]) * im[j];
+      for (int j = 0; j < CPT; ++j) if (wave_c(j)) z[j] = quotient(x[j] + tau * t[j] - tau * c[j], mi[j], im[j]);
       step_to(z, false);
       next_n();
       give_n(u);
@@ -601,9 +601,9 @@ __device__ __forceinline__ void run_resident(const Run& A, const DevProblem& P, 
 #pragma unroll
       for (int j = 0; j < CPT; ++j) {
         if (!wave_c(j)) break;
-        gp[j] = q[j] + c[j] + (x[j] - v[j]) * itau;
+        gp[j] = q[j] + c[j] + quotient(x[j] - v[j], tau, itau);
         up[j] = x[j];
-        z[j] = x[j] - alpha0 * gp[j] * im[j];
+        z[j] = x[j] - quotient(alpha0 * gp[j], mi[j], im[j]);
       }
       step_to(z, !jac);
       next_n();
@@ -619,7 +619,7 @@ __device__ __forceinline__ void run_resident(const Run& A, const DevProblem& P, 
         double g[CPT], alpha;
         mul_q(u, L.hu, q);
 #pragma unroll
-        for (int j = 0; j < CPT; ++j) if (wave_c(j)) g[j] = q[j] + c[j] + (u[j] - v[j]) * itau;
+        for (int j = 0; j < CPT; ++j) if (wave_c(j)) g[j] = q[j] + c[j] + quotient(u[j] - v[j], tau, itau);
         if (fuse) {
           const double den = L.scal[SL_SDG];
           alpha = den > 0.0 ? (jac ? L.scal[SL_SJS] : L.scal[SL_DELTA2]) / den : 1.0;
@@ -645,7 +645,7 @@ __device__ __forceinline__ void run_resident(const Run& A, const DevProblem& P, 
 #pragma unroll
         for (int j = 0; j < CPT; ++j) {
           if (!wave_c(j)) break;
-          z[j] = u[j] - alpha * g[j] * im[j];
+          z[j] = u[j] - quotient(alpha * g[j], mi[j], im[j]);
           up[j] = u[j];
         }
         step_to(z, !jac);
@@ -674,7 +674,7 @@ __device__ __forceinline__ void run_resident(const Run& A, const DevProblem& P, 
       if (!own_r(j)) continue;
       const double axb = 2.0 * aw[j] - Ax[j];
       if (bounded && lo[j] != hi[j]) {
-        const double q = axb - y[j] * isig;
+        const double q = axb - quotient(y[j], sigma, isig);
         wy[j] = sigma * (fmin(fmax(q, lo[j]), hi[j]) - q);
       } else {
         wy[j] = y[j] + sigma * (b[j] - axb);
