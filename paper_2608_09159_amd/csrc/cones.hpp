@@ -252,17 +252,19 @@ __device__ SocSol soc_wave_solve(const In& in, bool euclid, double* warm, int Lg
     if (psi < 0.0) lo = d; else hi = d;
     if (psi == 0.0) break;
     double dn = d - psi * rcp_step(dpsi);
-    // converged: the Newton correction is below the resolution of d (tested
-    // before the bracket test, since a converged step may land on the bracket
-    // end it has just set), or the next one would be
+    // converged: the Newton correction is below the resolution of d, or the
+    // next one would be (tested before the bracket test, since rounding may put
+    // a converged step on the wrong side of the end it has just set)
     const double st = fabs(dn - d);
-    const bool in_bracket = dn > lo && dn < hi;
-    if (st <= 4.0 * 2.220446049250313e-16 * d || (in_bracket && newton_done(st, prev, d))) {
-      d = dn;
+    if (st <= 4.0 * 2.220446049250313e-16 * d || newton_done(st, prev, d)) {
+      d = fmin(fmax(dn, lo), hi);
       break;
     }
-    prev = in_bracket ? st : 0.0;
-    if (!in_bracket) dn = isfinite(hi) ? 0.5 * (lo + hi) : 2.0 * fmax(d, lo);
+    prev = st;
+    if (!(dn > lo && dn < hi)) {
+      dn = isfinite(hi) ? 0.5 * (lo + hi) : 2.0 * fmax(d, lo);
+      prev = 0.0;
+    }
     if (isfinite(hi) && hi - lo <= 4.0 * 2.220446049250313e-16 * hi) {
       d = dn;
       break;
@@ -655,14 +657,14 @@ __device__ bool exp_newton(const ExpData& e, double rho, double out[3], double* 
     else hi = fmin(hi, rho);
     double rn = ok && dH > 0.0 ? rho - H * rcp_step(dH) : NAN;
     const double st = fabs(rn - rho), at = fmax(1.0, fabs(rho));
-    const bool in_bracket = rn > lo && rn < hi;
-    if (ok && (st <= 4.0 * 2.220446049250313e-16 * at || (in_bracket && newton_done(st, prev, at)))) {
+    if (ok && (st <= 4.0 * 2.220446049250313e-16 * at || newton_done(st, prev, at))) {
+      rn = fmin(fmax(rn, lo), hi);
       if (!exp_point_if(e, rn, out)) return false;
       if (warm) *warm = rn;
       return true;
     }
     prev = st;
-    if (!in_bracket) {
+    if (!(rn > lo && rn < hi)) {
       prev = 0.0;
       if (isfinite(lo) && isfinite(hi)) {
         if (hi - lo <= 8.9e-16 * at) return false;
@@ -781,12 +783,17 @@ __device__ __forceinline__ double pow_qroot(double s, double c) {
   return s >= 0.0 ? 0.5 * (s + d) : 2.0 * c / (d - s);
 }
 
+// the comparison itself, out of line: it is needed rarely, and two powers are long
+__device__ __noinline__ bool pow_reaches_near(double a, double b, double al, double c) {
+  return pow(a, al) * pow(b, 1.0 - al) >= c;
+}
+
 // a^al b^(1-al) >= c for a, b >= 0: by logarithms, each a third of a pow, unless
 // they are within their rounding (|log| ulps) of equality
 __device__ __forceinline__ bool pow_reaches(double a, double b, double al, double c) {
   const double p = al * log(a), q = (1.0 - al) * log(b), l = log(c), d = p + q - l;
   if (fabs(d) > 1e-14 * (1.0 + fabs(p) + fabs(q) + fabs(l))) return d > 0.0;
-  return pow(a, al) * pow(b, 1.0 - al) >= c;
+  return pow_reaches_near(a, b, al, c);
 }
 
 __device__ __forceinline__ void project_pow_body(double x, double y, double z, double al, double mx, double my,
@@ -836,15 +843,14 @@ __device__ __forceinline__ void project_pow_body(double x, double y, double z, d
     else break;
     double tn = (isfinite(g) && dg < 0.0) ? t - g * rcp_step(dg) : NAN;
     const double st = fabs(tn - t), at = fmax(1.0, fabs(t));
-    const bool in_bracket = tn > lo && tn < hi;
-    if (st <= 2.0 * 2.220446049250313e-16 * at || (in_bracket && newton_done(st, prev, at))) {   // converged
-      t = tn;
+    if (st <= 2.0 * 2.220446049250313e-16 * at || newton_done(st, prev, at)) {   // converged
+      t = fmin(fmax(tn, lo), hi);
       break;
     }
     prev = st;
     const bool closed = isfinite(lo) && isfinite(hi);
     // g_M levels off towards both ends, where a Newton step would run away
-    if (!in_bracket || (!closed && st > grow)) {
+    if (!(tn > lo && tn < hi) || (!closed && st > grow)) {
       prev = 0.0;
       if (closed) {
         if (hi - lo <= 2.0 * 2.220446049250313e-16 * at) break;
@@ -909,10 +915,12 @@ __device__ __forceinline__ void project_exp1_body(double z0, double t0, double m
     else { lo = hi = z; break; }
     double zn = (d > 0.0) ? z - fz * rcp_step(d) : 0.5 * (lo + hi);
     const double st = fabs(zn - z), at = fmax(1.0, fabs(z));
-    const bool in_bracket = zn > lo && zn < hi;
-    if (st <= 2.220446049250313e-16 * at || (in_bracket && newton_done(st, prev, at))) { lo = hi = zn; break; }   // converged
+    if (st <= 2.220446049250313e-16 * at || newton_done(st, prev, at)) {   // converged
+      lo = hi = fmin(fmax(zn, lo), hi);
+      break;
+    }
     prev = st;
-    if (!in_bracket) {
+    if (!(zn > lo && zn < hi)) {
       zn = 0.5 * (lo + hi);
       prev = 0.0;
     }
