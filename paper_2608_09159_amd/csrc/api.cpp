@@ -820,8 +820,8 @@ int upload_instance(Handle* h, Instance* I) {
       // up to 2 MB of buffers (a share of an XCD's L2 beside the matrices),
       // at least two: a buffer is filled while its predecessor is read
       V.nring = (int)std::min<long>(16, std::max<long>(2, (2L << 20) / (8 * (V.ld_n + V.ld_m))));
-      V.ring_n = B.alloc<double>((size_t)V.nring * V.ld_n);
-      V.ring_m = B.alloc<double>((size_t)V.nring * V.ld_m);
+      V.ring_n = ring_start(B.alloc<double>((size_t)V.nring * V.ld_n + RES_RING_ALIGN));
+      V.ring_m = ring_start(B.alloc<double>((size_t)V.nring * V.ld_m + RES_RING_ALIGN));
     }
     // skewed A^T row lengths (some row of a workgroup more than 16 times its
     // mean and longer than 64): order each workgroup's rows by length class

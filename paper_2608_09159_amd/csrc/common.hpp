@@ -103,6 +103,12 @@ constexpr int RES_CHUNK_MAX = 4096;   // products staged at a time
 constexpr int RES_LDS_STATIC = 32 * 1024;
 constexpr size_t RES_LDS_DYN = 160 * 1024 - RES_LDS_STATIC;
 constexpr int RES_RING_ALIGN = 32;    // doubles: a workgroup's part of a ring buffer starts a line
+// the first such start in an allocation that holds RES_RING_ALIGN more than it needs
+// (memory of a caller's allocator may begin anywhere)
+inline double* ring_start(double* p) {
+  const uintptr_t line = RES_RING_ALIGN * sizeof(double);
+  return reinterpret_cast<double*>((reinterpret_cast<uintptr_t>(p) + line - 1) / line * line);
+}
 
 // coordinates and rows of one workgroup, rank of R (0: its columns stay in
 // global memory), products staged; one: the whole problem on one workgroup
