@@ -39,6 +39,15 @@ __device__ __forceinline__ bool get_pair(const unsigned long long* p, unsigned e
   return (unsigned)a == ep && (unsigned)b == ep;
 }
 
+// This thread's stores are done.  The wait is not a fence to the compiler, so
+// nothing that touches memory may move across it: a store of an iterate that sank
+// below it would be published by the all-reduce before it is in memory.
+__device__ __forceinline__ void stores_done() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+  asm volatile("" ::: "memory");
+}
+
 struct GridTeam {
   Comm C;
   unsigned long long limit;
@@ -77,7 +86,7 @@ __device__ __forceinline__ bool allreduce(const GridTeam& T, LdsT& L, int ns, Sl
                                           bool acq) {
   const int tid = thread_here(), lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int G = T.size, me = T.rank;
-  __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this thread's stores are done
+  stores_done();
   if (tid == 0) {
     L.epoch += 1u;
     L.flag = 0;
