@@ -42,7 +42,10 @@
  *    pdhcg_result.status.
  *  - A handle is not thread-safe; use one handle per host thread.  All device
  *    work is issued on settings.stream (a hipStream_t passed as void*; NULL
- *    means the null stream).
+ *    means the null stream).  Solves of several threads of one process share a
+ *    device: launches whose workgroups are not all resident together take
+ *    turns.  Solves of separate processes on one device are not coordinated
+ *    and may end as PDHCG_ABORTED.
  */
 #ifndef PDHCG_H
 #define PDHCG_H

@@ -13,6 +13,7 @@
 #include "common.hpp"
 #include "host_setup.hpp"
 #include "pdhcg.h"
+#include "places.hpp"
 #include "solver.hpp"
 
 using namespace pdhcg;
@@ -225,6 +226,35 @@ DevSettings to_dev(const pdhcg_settings& s) {
   d.trace_iters = s.trace_iters;
   return d;
 }
+
+// the places of one launch on the current device, from before it until the host has
+// waited for it (one workgroup waits for no other and needs none)
+class LaunchPlaces {
+ public:
+  LaunchPlaces(int grid, int per, int cus) : hold_{grid, per} {
+    static Places devices[MAX_DEVICES];
+    int dev = 0;
+    if (grid <= 1 || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= MAX_DEVICES) return;
+    try {
+      devices[dev].take(hold_, cus, std::chrono::seconds(60));
+      places_ = &devices[dev];
+    } catch (...) {   // a lock failed: as without
+    }
+  }
+  ~LaunchPlaces() {
+    try {
+      if (places_) places_->give(hold_);
+    } catch (...) {
+    }
+  }
+  LaunchPlaces(const LaunchPlaces&) = delete;
+  LaunchPlaces& operator=(const LaunchPlaces&) = delete;
+
+ private:
+  static constexpr int MAX_DEVICES = 64;
+  Places::Hold hold_;
+  Places* places_ = nullptr;
+};
 
 // ---- the register-resident core (resident.hpp): which problems it takes
 bool res_settings(const Handle* h, const HostInstance& H) {
@@ -1716,11 +1746,16 @@ int pdhcg_solve(pdhcg_handle* h, const double* x0, const double* y0, pdhcg_resul
     }
     a.epoch = I->epoch;
     I->epoch = 0;
-    if (timing) HIPCHK(hipEventRecord(ev0, st));
-    HIPCHK(launch_solve(a, phase32, I->grid, st));
-    if (timing) HIPCHK(hipEventRecord(ev1, st));
-    HIPCHK(hipMemcpyAsync(&cb, I->ctl, sizeof(cb), hipMemcpyDeviceToHost, st));
-    HIPCHK(hipStreamSynchronize(st));
+    {
+      int per = 0, cus = 0;
+      HIPCHK(solver_room(a, phase32, I->grid, &per, &cus));
+      const LaunchPlaces held(I->grid, per, cus);
+      if (timing) HIPCHK(hipEventRecord(ev0, st));
+      HIPCHK(launch_solve(a, phase32, I->grid, st));
+      if (timing) HIPCHK(hipEventRecord(ev1, st));
+      HIPCHK(hipMemcpyAsync(&cb, I->ctl, sizeof(cb), hipMemcpyDeviceToHost, st));
+      HIPCHK(hipStreamSynchronize(st));
+    }
     c.status = launch_status(cb);
     if (c.status != PDHCG_ABORTED) I->epoch = c.epoch;
     ++nlaunch;

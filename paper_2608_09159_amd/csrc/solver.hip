@@ -2051,20 +2051,26 @@ static hipError_t allow_lds(const void* k, int bytes) {
                            : hipSuccess;
 }
 
+static const void* kernel_of(const KArgs& args, bool fp32, int grid) {
+  return solver_kernel_for(args.P.res, args.P.q_diag != 0, fp32, args.P.ext != 0, args.P.n_wave > 0 || args.P.n_lane > 0,
+                           grid);
+}
+
+hipError_t solver_room(const KArgs& args, bool fp32, int grid, int* per, int* cus) {
+  const void* k = kernel_of(args, fp32, grid);
+  int dev = 0;
+  hipError_t e = allow_lds(k, args.lds_bytes);
+  if (e == hipSuccess) e = hipGetDevice(&dev);
+  if (e == hipSuccess) e = hipDeviceGetAttribute(cus, hipDeviceAttributeMultiprocessorCount, dev);
+  if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(per, k, BLOCK, (size_t)args.lds_bytes);
+  if (e != hipSuccess) return e;
+  return (long)*per * (long)*cus < (long)grid ? hipErrorCooperativeLaunchTooLarge : hipSuccess;
+}
+
 hipError_t launch_solve(const KArgs& args, bool fp32, int grid, hipStream_t stream) {
   KArgs a = args;
   void* params[] = {&a};
-  const bool ext = args.P.ext != 0;
-  const bool cones = args.P.n_wave > 0 || args.P.n_lane > 0;
-  const void* k = solver_kernel_for(args.P.res, args.P.q_diag != 0, fp32, ext, cones, grid);
-  int dev = 0, ncu = 0, per = 0;
-  hipError_t e = allow_lds(k, args.lds_bytes);
-  if (e == hipSuccess) e = hipGetDevice(&dev);
-  if (e == hipSuccess) e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
-  if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k, BLOCK, (size_t)args.lds_bytes);
-  if (e != hipSuccess) return e;
-  if ((long)per * (long)ncu < (long)grid) return hipErrorCooperativeLaunchTooLarge;
-  return hipLaunchKernel(k, dim3(grid), dim3(BLOCK), params, (size_t)args.lds_bytes, stream);
+  return hipLaunchKernel(kernel_of(args, fp32, grid), dim3(grid), dim3(BLOCK), params, (size_t)args.lds_bytes, stream);
 }
 
 hipError_t max_resident_grid_for(bool fp32, bool ext, bool cones, int lds_bytes, int* out) {

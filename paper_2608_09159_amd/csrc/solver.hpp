@@ -7,6 +7,8 @@
 namespace pdhcg {
 
 int block_size();
+// whether a launch fits the device: workgroups of its kernel a CU, and CUs
+hipError_t solver_room(const KArgs& args, bool fp32, int grid, int* per, int* cus);
 hipError_t launch_solve(const KArgs& args, bool fp32, int grid, hipStream_t stream);
 // workgroups resident at once for the kernel(s) a solve of this kind runs
 hipError_t max_resident_grid_for(bool fp32, bool ext, bool cones, int lds_bytes, int* out);
