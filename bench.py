@@ -33,6 +33,7 @@ import json
 import math
 import os
 import sys
+import tempfile
 import time
 
 ROOT = os.path.dirname(os.path.abspath(__file__))
@@ -57,7 +58,7 @@ MEASURED_TRAFFIC = {
     # (degree coordinate order)
     "bytes_per_launch": 7783200183547.8,
 }
-KERNEL_SOURCES = ("solver.hip", "resident.hpp", "cones.hpp", "common.hpp", "api.cpp", "host_setup.cpp")
+KERNEL_SOURCES = ("solver.hip", "resident.hpp", "exchange.hpp", "cones.hpp", "common.hpp", "api.cpp", "host_setup.cpp")
 
 
 def kernel_sources_hash():
@@ -432,10 +433,17 @@ def timed_solves(prob, args, budget, precision="fp64", verbose=0):
     import paper_2608_09159_amd as pkg
     stream = torch.cuda.current_stream()
     extra = {"max_iter": budget} if budget > 0 else {}
-    t0 = time.perf_counter()
-    h = pkg.setup(prob, tol=args.tol, time_kernels=1, stream=stream.cuda_stream, precision=precision,
-                  verbose=verbose, **extra)
-    setup_s = time.perf_counter() - t0
+    with tempfile.TemporaryDirectory() as tmp:
+        dump = os.path.join(tmp, "partition.txt")
+        os.environ["PDHCG_PARTITION_DUMP"] = dump
+        try:
+            t0 = time.perf_counter()
+            h = pkg.setup(prob, tol=args.tol, time_kernels=1, stream=stream.cuda_stream, precision=precision,
+                          verbose=verbose, **extra)
+            setup_s = time.perf_counter() - t0
+        finally:
+            del os.environ["PDHCG_PARTITION_DUMP"]
+        timed_solves.core = int(np.loadtxt(dump, dtype=np.int64, ndmin=2)[0, 8])
     log(f"setup done ({setup_s:.1f} s, {precision})")
     for _ in range(args.warmup):
         w = h.solve()
@@ -449,21 +457,23 @@ def timed_solves(prob, args, budget, precision="fp64", verbose=0):
     return runs, wall, setup_s
 
 
-def solver_kernel_name(prob, precision, grid):
-    """The library's solver kernel for this solve: FP32 bulk, one workgroup,
-    the register-resident core, the implementation-form features (row
-    bounds, boxes, fixed-middle EXP), or, without cone blocks, the cone-free kernel at two workgroups per CU."""
+def solver_kernel_name(prob, precision, grid, core):
+    """The library's solver kernel for this solve: FP32 bulk, the register-resident
+    core (`core`, the partition dump's last column: 1 and 2 for one and two
+    coordinates a thread on a grid, 3 on one workgroup), one workgroup, the
+    implementation-form features (row bounds, boxes, fixed-middle EXP), or, without
+    cone blocks, the cone-free kernel at two workgroups per CU."""
     kinds = {k for k, _, _, _ in prob.cones}
     ext = getattr(prob, "row_lo", None) is not None or bool(kinds & {"box", "exp1"})
     cones = bool(kinds & {"soc", "rsoc", "exp", "pow", "exp1"})
     if precision == "fp32":
         return "solve_kernel_f32" + ("" if cones else "_lin") + ("_ext" if ext else "")
-    # register-resident core: at most 512 coordinates and rows on one
-    # workgroup, about 1,024 of each a workgroup on a grid
-    if grid == 1 and max(prob.n, prob.m) <= 512:
+    if core == 3:
         return "resident_kernel_one"
-    if grid > 1 and max(prob.n, prob.m) <= 900 * grid:
-        return "resident_kernel"
+    if core:
+        P = getattr(prob, "P", None)
+        diag = prob.R is None and (P is None or np.array_equal(P.tocsr().indices, np.arange(P.shape[0])))
+        return f"resident_kernel{core}" + ("" if cones else "_lin") + ("_diag" if diag else "")
     if grid == 1:
         return "solve_kernel_one_ext" if ext else "solve_kernel_one"
     if ext:
@@ -675,6 +685,7 @@ def main():
         del src, dst
     log(f"{wname}: instance generated")
     runs, wall, setup_s = timed_solves(prob, args, budget)
+    core = timed_solves.core
     log(f"{wname}: {args.steps} timed solves in {wall:.2f} s (setup {setup_s:.1f} s)")
     iters = sum(r["iterations"] for r in runs)
     inner = sum(r["inner_iterations"] for r in runs)
@@ -718,7 +729,7 @@ def main():
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
                      "traffic_unit": "bytes per launch (rocprofv3 FETCH_SIZE+WRITE_SIZE, copy-calibrated)",
-                     "kernel": solver_kernel_name(prob, "fp64", grid), "kernel_avg_launch_ms": 1e3 * ksum / launches,
+                     "kernel": solver_kernel_name(prob, "fp64", grid, core), "kernel_avg_launch_ms": 1e3 * ksum / launches,
                      "launch": [grid, runs[-1]["block_dim"]],
                      "algorithmic_bytes_per_iteration": alg_bytes / iters,
                      "bytes_model": "method (A, A^T, P read once per product, ideal gathers)"},
