@@ -18,8 +18,9 @@
 //    rotation U of eq. rsoc-via-soc.  The root lies below or above q/2 in the
 //    xi of eq. rsoc-metric-projection exactly when p > 0 or p < 0.
 //  EXP (eq. exp-metric-projection): the root of h_M on the set of ratios
-//    rho whose ray is visible from r and carries eta_M > 0, bisected on the
-//    cancellation-free H = h_M * Den; special cases as printed.
+//    rho whose ray is visible from r and carries eta_M > 0, on the
+//    cancellation-free H = h_M * Den: Newton inside a sign bracket, and a
+//    bisection where that ends elsewhere; special cases as printed.
 //  POW: the root of g_M over (0, R) (Prop. power-cone-bisection) by Newton in
 //    the logit of rho / R inside the sign bracket, with the stable quadratic
 //    root of eq. power-cone-stable-quadratic-root.

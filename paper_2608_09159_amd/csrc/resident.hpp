@@ -18,7 +18,7 @@
 // Bound by latency: two to three products and three to six all-reduces an
 // iteration, 2.5 to 3 us each, in sequence.  Whole solves, run_solver with a
 // counting barrier and separate sums before, this core after: 200 coordinates
-// and 256 iterations on one workgroup 10.0 to 5.5 ms; sparse Q, 20,011
+// and 256 iterations on one workgroup 10.0 to 5.6 ms; sparse Q, 20,011
 // coordinates 3.6 to 1.8 ms; boxes and row bounds, 60,001 coordinates 5.7 to
 // 2.5 ms; all cones with rank-10 Q, 100,000 coordinates 8.8 to 5.0 ms.
 #pragma once

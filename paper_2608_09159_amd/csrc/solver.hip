@@ -6,10 +6,11 @@
 // so every per-coordinate step -- prox, cone projections, Halpern update --
 // is local to the workgroup and needs only __syncthreads.  Grid barriers
 // remain only where a global reduction or a gather over all coordinates is
-// needed.  Every reduction is written as one partial per workgroup and
-// re-reduced by every workgroup in the same fixed order (deterministic and
-// identical everywhere), so all workgroups take the same control decisions
-// (inner stop, restart, termination) without a host round trip.
+// needed.  A reduction carries the barrier (exchange.hpp): each workgroup
+// stores one partial, the sums are formed once in workgroup order by their
+// owners and read back by all, so they are deterministic and the same bits
+// everywhere, and all workgroups take the same control decisions (inner stop,
+// restart, termination) without a host round trip.
 //
 // Outer iteration (reflected-Halpern epoch, eq. stored-pdhg-candidate and
 // eq. rh-update; primal-first PDHG operator eq. theory-pdhg-map):
