@@ -35,7 +35,7 @@ Passages followed
   scaled to the block's coordinates; KKT terms from the set's recession
   cone and support function (exp1_dual_terms).
 
-Readings where the paper is silent (each also listed in the design doc):
+Readings where the paper is silent:
 * ||A||_2 by 128 power iterations on A^T A from 1/sqrt(n) (overridable);
   a zero estimate (A = 0 or no rows) is replaced by 1;
 * omega_0 = ||c^||/||b^|| when both exceed 1e-10, else 1 (overridable);
